@@ -1,4 +1,4 @@
-// bf16 GEMM on CDNA4 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation,
+// bf16 GEMM on CDNA4 matrix cores (v_mfma_f32_16x16x32_bf16), fp32 accumulation,
 // with the fused epilogues of a decoder layer's projections.
 //
 //   C(m, n) = sum_k A(m, k) B(n, k)
@@ -6,13 +6,22 @@
 //   B(n, k) = B_K ? B[n*ldb + k] : B[k*ldb + n]
 //
 // Tile: 256 x 256 per workgroup of 512 threads (8 waves, 4 along m x 2 along
-// n); each wave owns 64 x 128 = 2 x 4 MFMA blocks of 32 x 32. K is walked in
+// n); each wave owns 64 x 128 = 4 x 8 MFMA blocks of 16 x 16. K is walked in
 // stages of 64: LDS holds two 64 KiB stages (A 256 x 64 | B 256 x 64); while
 // the waves multiply stage s, stage s + 1 streams in from HBM/L2, and one
 // barrier per stage both publishes the new stage and frees the old one.
 // Waves 0-3 stream A, waves 4-7 stream B (8 loads of 1 KiB per wave per
-// stage). A stage is multiplied in two halves of k = 32 (fragments of one
-// half in registers at a time).
+// stage). A stage is multiplied in four steps (k half, row half), the fragments
+// of the next step read while one multiplies.
+//
+// What bounds it: the chip's power limit. Full-size products run at 1.9-2.0 GHz
+// of the nominal 2.4, and with the stage's loads left out the clock rises to
+// 2.25 GHz while the cycle count falls only 11%. Hence the 16 x 16 x 32
+// instruction: the same rate per cycle as 32 x 32 x 16 but half the accumulator
+// traffic per product, and a register-only loop on normal data sustains 2110
+// TFLOP/s with it against 1848 with 32 x 32 x 16. Over the twelve products of a
+// d 4096 / FFN 11008 / 4096-token layer: 4271 us against 4453 (the 4096^3 NT
+// product at 2.02 GHz instead of 1.89).
 //
 // Operand tiles go from HBM straight into LDS (buffer_load_dwordx4 ... lds:
 // lane l of a wave's load fills bytes [16 l, 16 l + 16) of a 1 KiB LDS run),
@@ -22,33 +31,33 @@
 // descriptors make out-of-range lanes (matrix edges, K tail) read zeros.
 //   k-major operand: LDS rows of 64 k (128 B, one full cache line of the
 //     operand row per 8-lane group, lanes in address order). Load run q
-//     (0..31) holds tile rows q, q + 32, ..., q + 224, and runs sit 1040 bytes
-//     apart, so tile row 32 p + q is at q * 1040 + 128 p. A fragment (32 rows
-//     at one k chunk, 16 bytes per lane) is one ds_read_b128 of 32 runs at one
-//     position, and the 16-byte run padding makes every 16 lanes touch all 64
-//     banks once. (An earlier layout kept runs of 8 consecutive rows and
-//     XOR-swizzled the 16-byte chunks of each cache line across the lanes of
-//     a load, and the m/n-major one below XOR-swizzled 64-byte blocks: both
-//     conflict-free too, but every product ran 3-6% slower with them. Rows of
-//     32 k, i.e. half cache lines per load, cost a third of the throughput of
-//     the global->LDS path.)
+//     (0..31) holds tile rows q, q + 32, ..., q + 224, and runs sit 1056 bytes
+//     apart, so tile row 32 p + q is at q * 1056 + 128 p. A fragment (16 rows,
+//     four 16-byte k chunks) is one ds_read_b128. It is served in phases of 16
+//     lanes, {0-3, 12-15, 20-27} and so on: rows 0-3 and 12-15 of one chunk with
+//     rows 4-11 of the next, so a run distance of 2 chunks mod 16 (32 bytes of
+//     padding) makes each phase touch all 64 banks once. (A distance of one
+//     chunk, right for 32-row fragments, collides here. Rows of 32 k, i.e. half
+//     cache lines per load, cost a third of the throughput of the global->LDS
+//     path.)
 //   m/n-major operand (a weight read as dX = dY W, both operands of a weight
 //     gradient dW = dY^T X): LDS rows of one k and 256 m (512 B, lanes in
-//     address order); run q holds k rows q and q + 32, runs sit 1088 bytes
-//     apart, so the four k rows one transposing read spans fall on different
-//     banks. The fragment is read with the CDNA4
-//     transposing load ds_read_b64_tr_b16: in each group of 16 lanes, lane j
-//     receives element j % 4 of the 8 bytes addressed by lane 4e + j / 4 as its
-//     element e, so lanes addressing four consecutive k rows at four 4-element
-//     column runs receive one column's four k values each. Two such loads
-//     give the 8 k values of the MFMA operand; no transposed copy exists in
-//     HBM and no register shuffles are spent.
+//     address order); run q holds k rows swap23(q) and swap23(q) + 32 (swap23
+//     exchanges bits 2 and 3), runs sit 1056 bytes apart. The fragment is read
+//     with the CDNA4 transposing load ds_read_b64_tr_b16: in each group of 16
+//     lanes, lane j receives element j % 4 of the 8 bytes addressed by lane
+//     4e + j / 4 as its element e, so lanes addressing four consecutive k rows
+//     at four 4-element column runs receive one column's four k values each.
+//     Two such loads (k rows 8g + [0, 4) and 8g + 4 + [0, 4) for lane group g)
+//     give the 8 k values of the MFMA operand; swap23 puts the eight k rows that
+//     32 lanes address in one phase into eight consecutive runs, 32 bytes apart
+//     in the banks. No transposed copy exists in HBM and no register shuffles
+//     are spent.
 //
 // The MFMA is issued with B's fragment in the instruction's first operand and
-// A's in the second, which leaves lane l holding output row m = l % 32 and four
-// runs of four consecutive columns n = 8g + 4(l / 32) + e: epilogues store 8 or
-// 16 contiguous bytes per lane, and the column pairs (c, c + 64) that RoPE and
-// SwiGLU combine sit in the same lane (blocks j and j + 2 of a 128-wide wave).
+// A's in the second, which leaves lane l holding output row m = l % 16 and four
+// consecutive columns n = 4(l / 16) + e of each block; the column pairs (c, c +
+// 64) that RoPE and SwiGLU combine sit in one wave (blocks j and j + 4).
 // Output, residual and gate/up element types are run-time values (uniform
 // branches in the epilogue only), except in the instantiations for the decoder
 // stage's own type mix (EpiTypes below), where they are compile-time constants.
@@ -63,12 +72,11 @@ constexpr int BM = 256, BN = 256;
 constexpr int KS = 64;             // k per stage
 constexpr int NT = 512;            // threads per workgroup (8 waves)
 constexpr int WM = 64, WN = 128;   // wave tile
-constexpr int FM = WM / 32, FN = WN / 32;
-// LDS-DMA runs: one 1 KiB load per wave instruction, with 16 bytes of padding
-// after each run of a k-major operand and 64 after each run of an m/n-major one.
-constexpr int RUN_K = 1024 + 16;
-constexpr int RUN_MN = 1024 + 64;
-constexpr int OPND_BYTES = 32 * RUN_MN;       // one operand's stage in LDS (32 runs)
+constexpr int FM = WM / 16, FN = WN / 16;  // 16 x 16 MFMA blocks of a wave
+// LDS-DMA runs: one 1 KiB load per wave instruction, 32 bytes of padding after
+// each run.
+constexpr int RUN = 1024 + 32;
+constexpr int OPND_BYTES = 32 * RUN;       // one operand's stage in LDS (32 runs)
 constexpr int STAGE_BYTES = 2 * OPND_BYTES;   // A | B
 constexpr uint32_t OOB = 0x80000000u;    // buffer offset beyond every operand: reads 0
 
@@ -146,17 +154,16 @@ __device__ __forceinline__ void dma16s(i32x4_v rs, lds_t *lds, uint32_t voff, ui
 //     ROWMAP 1 (SwiGLU B rows): tile row r -> gate row ob + (r>>7)*64 + (r&63)
 //       for (r&127) < 64, else up row lim + ob + (r>>7)*64 + (r&63); valid
 //       while the output column ob + (r>>7)*64 + (r&63) < lim.
-//   m/n-major: run q = k rows q and q + 32; lane l -> k row q + 32 (l/32),
-//     global columns 8 (l%32) .. +7.
-// Run t of wave w is q = 8w + t: consecutive runs are one row (k-major) or one
-// k row (m/n-major) apart in the operand. The per-lane state is a row offset,
+//   m/n-major: run q = k rows swap23(q) and swap23(q) + 32; lane l -> k row
+//     swap23(q) + 32 (l/32), global columns 8 (l%32) .. +7.
+// Run t of wave w is q = 8w + t. The per-lane state is a row offset,
 // an in-row offset, a validity mask and a k position; everything else is
 // wave-uniform.
 template <bool KMAJ, int ROWMAP>
 struct Stream {
   uint32_t base;     // byte offset of run 0's row (k-major) or k row (m/n-major)
   uint32_t col[2];   // byte offset inside the row for even / odd runs
-  uint32_t run;      // byte distance between consecutive runs
+  uint32_t run;      // byte distance between two rows (k-major) or k rows
   uint32_t kb;       // bytes per unit of k
   uint32_t rows;     // bit t set when run t's row / columns are inside the operand
   int kl[2];         // k-major: first k of this lane's chunk; m/n-major: k row
@@ -185,7 +192,8 @@ struct Stream {
       kb = 2;
     } else {
       static_assert(ROWMAP == 0, "row remap needs a k-major operand");
-      const int kr0 = 8 * wave + 32 * (lane >> 5);  // k row of run 0
+      // k row of run 0: run q holds k rows swap23(q) and swap23(q) + 32
+      const int kr0 = 4 * (wave & 1) + 16 * (wave >> 1) + 32 * (lane >> 5);
       const int gm = base_row + 8 * (lane & 31);    // first of the lane's 8 columns
       kl[0] = kl[1] = kr0;
       rows = gm < lim ? 0xFFu : 0u;
@@ -196,21 +204,23 @@ struct Stream {
     }
   }
 
+  // rows (k-major) or k rows between run t and run 0
+  __device__ __forceinline__ static uint32_t step(int t) { return KMAJ ? t : (t & 3) + 8 * (t >> 2); }
   // each run's per-lane byte offset at k = k0 (OOB for lanes outside the
   // operand's rows or columns); valid for stages that end at or before K
   __device__ __forceinline__ void offsets(uint32_t vo[8], int k0) const {
 #pragma unroll
     for (int t = 0; t < 8; ++t)
-      vo[t] = (rows >> t) & 1u ? base + t * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
+      vo[t] = (rows >> t) & 1u ? base + step(t) * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
   }
   // run t of the wave's 8 runs of the stage starting at k0, into `lds` (the
   // operand's stage), every lane checked against K
   __device__ __forceinline__ void load1(i32x4_v rs, lds_t *lds, int wave, int k0, int K, int t) const {
     bool ok = (rows >> t) & 1u;
     if constexpr (KMAJ) ok = ok && k0 + kl[t & 1] < K;
-    else ok = ok && k0 + kl[0] + t < K;
-    const uint32_t off = ok ? base + t * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
-    dma16(rs, lds + (8 * wave + t) * (KMAJ ? RUN_K : RUN_MN), off);
+    else ok = ok && k0 + kl[0] + (int)step(t) < K;
+    const uint32_t off = ok ? base + step(t) * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
+    dma16(rs, lds + (8 * wave + t) * RUN, off);
   }
   __device__ __forceinline__ void load(i32x4_v rs, lds_t *lds, int wave, int k0, int K) const {
 #pragma unroll
@@ -218,22 +228,20 @@ struct Stream {
   }
 };
 
-// MFMA operand of 32 rows (row0 .. row0+31) at k = 16 s + 8 (lane / 32) + [0, 8)
-// of the stage stored at t (s = 0 .. 3)
+// MFMA operand of 16 rows (row0 .. row0+15) at k = 32 s + 8 (lane / 16) + [0, 8)
+// of the stage stored at t (s = 0, 1)
 template <bool KMAJ>
 __device__ __forceinline__ bf16x8_v frag(const lds_t *t, int row0, int s, int lane) {
   if constexpr (KMAJ) {
-    // tile row row0 + i (row0 a multiple of 32) is position row0 / 32 of run i
-    const int c = 2 * s + (lane >> 5);
-    return *reinterpret_cast<const lds_v8 *>(t + (lane & 31) * RUN_K + (row0 >> 5) * 128 + c * 16);
+    // tile row r is position r / 32 of run r % 32
+    return *reinterpret_cast<const lds_v8 *>(t + ((lane & 15) + (row0 & 16)) * RUN + (row0 >> 5) * 128 +
+                                             s * 64 + (lane >> 4) * 16);
   } else {
-    // k row k is position k / 32 of run k % 32
+    // k row k is position k / 32 of run swap23(k % 32)
     const int i16 = lane & 15, g = lane >> 4;
-    const int m = row0 + 16 * (g & 1) + 4 * (i16 & 3);
-    const int k = 16 * s + 8 * (g >> 1) + (i16 >> 2);
-    const lds_t *p0 = t + (k & 31) * RUN_MN + (k >> 5) * 512 + m * 2;
+    const lds_t *p0 = t + ((i16 >> 2) + 4 * (g & 1) + 16 * (g >> 1)) * RUN + s * 512 + (row0 + 4 * (i16 & 3)) * 2;
     const s16x4_v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p0));
-    const s16x4_v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p0 + 4 * RUN_MN));
+    const s16x4_v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p0 + 8 * RUN));
     const s16x4_v v[2] = {lo, hi};
     return __builtin_bit_cast(bf16x8_v, v);
   }
@@ -321,13 +329,11 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   }
   const int n0 = SWI ? tn * (BN / 2) : tn * BN;  // first output column
 
-  f32x16_v acc[FM][FN];
+  f32x4_v acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_v{0.0f, 0.0f, 0.0f, 0.0f};
 
   lds_t *const R0 = LDS_AS(char, ring);
   const int ns = (kend - kbeg + KS - 1) / KS;  // stages
@@ -345,8 +351,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   else sb_.offsets(vo, kbeg);
   const bool gk = grp == 0 ? A_K : B_K;
   const uint32_t kbw = gk ? 2u : (uint32_t)((grp == 0 ? p.lda : p.ldb) * 2);
-  const int runb = gk ? RUN_K : RUN_MN;
-  lds_t *const dst0 = R0 + grp * OPND_BYTES + 8 * w4 * runb;
+  lds_t *const dst0 = R0 + grp * OPND_BYTES + 8 * w4 * RUN;
   const bool ragged = (kend - kbeg) % KS != 0;
   auto load = [&](int st) {  // this group's operand of stage st
     if (ragged && st == ns - 1) {
@@ -358,61 +363,60 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
     lds_t *d = dst0 + (st & 1) * STAGE_BYTES;
     const uint32_t so = (uint32_t)(st * KS) * kbw;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) dma16s(rs, d + t * runb, vo[t], so);
+    for (int t = 0; t < 8; ++t) dma16s(rs, d + t * RUN, vo[t], so);
   };
 
-  typedef bf16x8_v FragA[FM];
-  typedef bf16x8_v FragB[FN];
-  // fragments of k-step q (k 16q .. 16q + 15) of stage st
-  auto read_step = [&](int st, int q, FragA &af, FragB &bfr) {
-    const lds_t *stage = R0 + (st & 1) * STAGE_BYTES;
+  // A stage is multiplied in four steps of 16 MFMAs: k half q (32 k), row half h
+  // of the wave's 64 rows.
+  bf16x8_v fa[FM], fb[2][FN];
+  auto read_a = [&](int st, int q, int h) {
+    const lds_t *t = R0 + (st & 1) * STAGE_BYTES;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) af[i] = frag<A_K>(stage, wm * WM + i * 32, q, lane);
-#pragma unroll
-    for (int jj = 0; jj < FN; ++jj) bfr[jj] = frag<B_K>(stage + OPND_BYTES, wn * WN + jj * 32, q, lane);
+    for (int i = 0; i < FM / 2; ++i) fa[2 * h + i] = frag<A_K>(t, wm * WM + (2 * h + i) * 16, q, lane);
   };
-  auto multiply = [&](const FragA &af, const FragB &bfr) {
+  auto read_b = [&](int st, int q) {
+    const lds_t *t = R0 + (st & 1) * STAGE_BYTES + OPND_BYTES;
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int j = 0; j < FN; ++j) fb[q][j] = frag<B_K>(t, wn * WN + j * 16, q, lane);
+  };
+  auto multiply = [&](int q, int h) {
 #pragma unroll
-      for (int jj = 0; jj < FN; ++jj)
-        acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[jj], af[i], acc[i][jj], 0, 0, 0);
+    for (int i = 2 * h; i < 2 * h + 2; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[q][j], fa[i], acc[i][j], 0, 0, 0);
   };
-  // LDS reads of one k-step: one per k-major fragment, two per m/n-major one
-  constexpr int NRD = (A_K ? FM : 2 * FM) + (B_K ? FN : 2 * FN);
-  constexpr int NMF = FM * FN;
-  auto interleave = [&]() {
-    interleave_steps<NRD, NMF>();
-    __builtin_amdgcn_sched_barrier(0);
-  };
-
-  // Software pipeline over k-steps: the fragments of step q + 1 are read
-  // while step q multiplies (two fragment sets in registers). Stage s + 1 goes
-  // into the buffer of stage s - 1, whose last fragments every wave has read
-  // before the barrier that published stage s. The barrier that publishes
-  // stage s + 1 (after each wave's wait for its own loads and reads) sits
-  // before the last k-step of stage s, so the first reads of stage s + 1
-  // overlap that k-step's MFMAs.
-  FragA fa[2];
-  FragB fb[2];
+  constexpr int RDA = A_K ? 2 : 4, RDB = B_K ? FN : 2 * FN;  // LDS reads of half A's, of B's fragments
   if (ns > 0) load(0);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   __syncthreads();
-  if (ns > 0) read_step(0, 0, fa[0], fb[0]);
+  if (ns > 0) {
+    read_a(0, 0, 0);
+    read_b(0, 0);
+  }
   for (int st = 0; st < ns; ++st) {
     if (st + 1 < ns) load(st + 1);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      read_step(st, q + 1, fa[(q + 1) & 1], fb[(q + 1) & 1]);
-      multiply(fa[q & 1], fb[q & 1]);
-      interleave();
-    }
+    read_a(st, 0, 1);
+    multiply(0, 0);
+    interleave_steps<RDA, 16>();
+    __builtin_amdgcn_sched_barrier(0);
+    read_a(st, 1, 0);
+    read_b(st, 1);
+    multiply(0, 1);
+    interleave_steps<RDA + RDB, 16>();
+    __builtin_amdgcn_sched_barrier(0);
+    read_a(st, 1, 1);
+    multiply(1, 0);
+    interleave_steps<RDA, 16>();
+    __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
     __syncthreads();
     // (after the last stage this reads the other buffer's stale data, unused)
-    read_step(st + 1, 0, fa[0], fb[0]);
-    multiply(fa[1], fb[1]);
-    interleave();
+    read_a(st + 1, 0, 0);
+    read_b(st + 1, 0);
+    multiply(1, 1);
+    interleave_steps<RDA + RDB, 16>();
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // ------------------------------------------------------------ epilogue
@@ -424,7 +428,6 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   // rows of 128 columns, or four rows of two 64-column halves, per
   // instruction). Loads of a group of rows are issued before its stores.
   __syncthreads();  // every wave's last fragment reads are done
-  const int frow = lane & 31, fhalf = lane >> 5;
   lds_t *const E = R0 + wave * 16384;
   typedef EpiTypes<EPI, TM> ET;
   const int c_dt = ET::C >= 0 ? ET::C : p.c_dt, r_dt = ET::R >= 0 ? ET::R : p.r_dt,
@@ -435,12 +438,11 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   // 32-row block i of the wave's results into its LDS staging area
   auto stage_block = [&](int i) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+    for (int f = 0; f < 2; ++f)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int c = 8 * j + 2 * g + fhalf;
-        const f32x4_t w = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-        *reinterpret_cast<lds_f4 *>(E + frow * 512 + ((c ^ (frow & 15)) << 4)) = w;
+      for (int j = 0; j < FN; ++j) {
+        const int r = 16 * f + (lane & 15), c = 4 * j + (lane >> 4);
+        *reinterpret_cast<lds_f4 *>(E + r * 512 + ((c ^ (r & 15)) << 4)) = acc[2 * i + f][j];
       }
   };
   auto chunk = [&](int r, int c) -> float4 {
@@ -449,7 +451,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   };
   if constexpr (EPI == LC_EPI_ROPE || EPI == LC_EPI_SWIGLU) {
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
+    for (int i = 0; i < WM / 32; ++i) {
       const int mrow0 = m0 + wm * WM + i * 32;
       stage_block(i);
       {
@@ -520,7 +522,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
     // loads and stores retire in issue order, so a wait for a load then never
     // waits for an earlier store.
     constexpr bool LD = EPI == LC_EPI_RESIDUAL || EPI == LC_EPI_ACCUM_F32 || EPI == LC_EPI_SWIGLU_BWD;
-    constexpr int PU = 4, PPB = 16 / PU, NP = FM * PPB;
+    constexpr int PU = 4, PPB = 16 / PU, NP = WM / 32 * PPB;
     const int q = lane & 31;
     const int n = ncol0 + 4 * q;
     const int ncl = n < p.N ? n : p.N - 4;  // loads of columns past N read valid data (unused)
