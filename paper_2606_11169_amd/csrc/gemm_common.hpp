@@ -1,0 +1,171 @@
+// Device code shared by the bf16 GEMM kernels: launch parameters, LDS-DMA
+// loads, tile lookup and the epilogue type mixes.
+#pragma once
+
+#include "common.hpp"
+
+#include <type_traits>
+
+namespace lc {
+
+struct GemmP {
+  const bf16_t *A;
+  const bf16_t *B;
+  void *C;
+  const void *R;
+  void *aux0;
+  void *aux1;
+  const float *rcos;
+  const float *rsin;
+  int64_t lda, ldb, ldc, ldr, ld_aux;
+  uint32_t a_bytes, b_bytes;  // byte extent of each operand (< 2^31)
+  int M, N, K;  // N: output columns (SwiGLU: gate/up width)
+  int tiles_m, tiles_n;
+  int group;  // tile-rows per group of the tile walk
+  int gmode, ngroups;
+  const int32_t *goff;
+  int64_t gstride_b, gstride_c;
+  int rope_seq, rope_cols;
+  int c_dt, r_dt, aux_dt;
+};
+
+namespace {
+
+constexpr int RUN = 1024 + 32;  // LDS-DMA runs: one 1 KiB load per wave instruction, 32 bytes of padding
+constexpr uint32_t OOB = 0x80000000u;    // buffer offset beyond every operand: reads 0
+
+typedef __attribute__((ext_vector_type(4))) short s16x4_v;
+// LDS addresses stay 32-bit LDS-space pointers throughout (no generic pointers)
+typedef __attribute__((address_space(3))) char lds_t;
+typedef __attribute__((address_space(3))) bf16x8_v lds_v8;
+typedef __attribute__((address_space(3))) s16x4_v lds_v4;
+#define LDS_AS(T, ptr) ((__attribute__((address_space(3))) T *)(ptr))
+
+typedef __attribute__((ext_vector_type(4))) int i32x4_v;
+
+// Raw buffer descriptor (CDNA: dword3 = 0x00020000, stride 0): offsets past
+// `bytes` read as zero.
+__device__ __forceinline__ i32x4_v make_rsrc(const void *base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  i32x4_v r;
+  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu));
+  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
+  r[3] = 0x00020000;
+  return r;
+}
+
+// 16 bytes per lane from the buffer at byte offset `off` into LDS at
+// lds + 16 * lane. Issued as inline assembly: the compiler then does not track
+// the load, so it inserts no wait for it before LDS reads of the other stage;
+// the step's explicit wait before its barrier is what orders it.
+__device__ __forceinline__ void dma16(i32x4_v rs, lds_t *lds, uint32_t off) {
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+               :
+               : "v"(off), "s"(rs), "s"(m0)
+               : "memory", "m0");
+}
+
+// The same with a wave-uniform part of the offset in the instruction's scalar
+// offset. The hardware checks only the per-lane offset against the buffer's
+// size, so callers use it where every lane's whole offset is inside the
+// operand or the lane's own offset is OOB.
+__device__ __forceinline__ void dma16s(i32x4_v rs, lds_t *lds, uint32_t voff, uint32_t soff) {
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :
+               : "v"(voff), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(m0)
+               : "memory", "m0");
+}
+
+// Scheduling pattern for one k-step: the NRD LDS reads of the next k-step
+// spread over the NMF MFMAs of this one (reads first, as evenly as possible).
+template <int NRD, int NMF, int I = 0>
+__device__ __forceinline__ void interleave_steps() {
+  if constexpr (I < NMF) {
+    constexpr int r = NRD / NMF + (I < NRD % NMF ? 1 : 0);
+    if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);  // LDS reads
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
+    interleave_steps<NRD, NMF, I + 1>();
+  }
+}
+
+// Element types of an epilogue's tensors: TM = 0 takes them from the run-time
+// values in GemmP (uniform branches around every access); TM = 1 fixes them to
+// the decoder stage's own mix for EPI (the branch-free accesses let the
+// compiler keep the epilogue's loads in flight instead of waiting at each
+// branch): residual add fp32 R and C, SwiGLU and its backward fp32 gate/up and
+// bf16 C, RoPE fp16 C and bf16 copy. The host takes TM = 1 when the call's
+// types are exactly that mix.
+template <int EPI, int TM>
+struct EpiTypes {
+  static constexpr bool RES = EPI == LC_EPI_RESIDUAL, SWI = EPI == LC_EPI_SWIGLU || EPI == LC_EPI_SWIGLU_BWD;
+  static constexpr bool ROPE = EPI == LC_EPI_ROPE;
+  static constexpr int C = TM == 0 ? -1 : RES ? LC_FP32 : SWI ? LC_BF16 : ROPE ? LC_FP16 : -1;
+  static constexpr int R = TM == 0 ? -1 : RES ? LC_FP32 : -1;
+  static constexpr int X = TM == 0 ? -1 : SWI ? LC_FP32 : ROPE ? LC_BF16 : -1;
+};
+
+// Where a workgroup's tile lies: false when it has none (uniform across the
+// workgroup). Workgroups are dispatched round-robin over the 8 XCDs; each XCD
+// gets a contiguous run of tiles, walked in groups of p.group tile-rows
+// (chosen by the host) so that neighbouring workgroups share A rows and B
+// columns in the XCD's L2.
+struct Tile {
+  int m0, tn;         // first row, tile column
+  int m_lim;          // rows at or past it are not this tile's
+  int kbeg, kend;
+  const bf16_t *B;
+  void *C;
+};
+template <int BM>
+__device__ __forceinline__ bool find_tile(const GemmP &p, Tile &t) {
+  int wg = blockIdx.x;
+  const int nwg = gridDim.x;
+  if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
+  t.m_lim = p.M;
+  t.kbeg = 0;
+  t.kend = p.K;
+  t.B = p.B;
+  t.C = p.C;
+  if (p.gmode == LC_GROUP_ROWS) {
+    // tile slot wg / tiles_n walks the groups' row tiles in order; slots past
+    // the last group's tiles have nothing to do (the grid is an upper bound)
+    t.tn = wg % p.tiles_n;
+    int slot = wg / p.tiles_n, g = 0, lo = 0, hi = 0;
+    for (; g < p.ngroups; ++g) {
+      lo = min(max(p.goff[g], 0), p.M);
+      hi = min(max(p.goff[g + 1], lo), p.M);
+      const int nt = (hi - lo + BM - 1) / BM;
+      if (slot < nt) break;
+      slot -= nt;
+    }
+    if (g == p.ngroups) return false;
+    t.m0 = lo + slot * BM;
+    t.m_lim = hi;
+    t.B = p.B + (int64_t)g * p.gstride_b;
+    return true;
+  }
+  if (p.gmode == LC_GROUP_K) {
+    const int per = p.tiles_m * p.tiles_n, g = wg / per;
+    wg -= g * per;
+    t.kbeg = min(max(p.goff[g], 0), p.K);
+    t.kend = min(max(p.goff[g + 1], t.kbeg), p.K);
+    t.C = static_cast<char *>(p.C) + (int64_t)g * p.gstride_c * (p.c_dt == LC_FP32 ? 4 : 2);
+  }
+  const int per_group = p.group * p.tiles_n;
+  const int first_m = (wg / per_group) * p.group;
+  const int gsz = min(p.tiles_m - first_m, p.group);
+  t.m0 = (first_m + (wg % per_group) % gsz) * BM;
+  t.tn = (wg % per_group) / gsz;
+  return true;
+}
+
+}  // namespace
+
+// k_gemm_tile.hip: the products whose grid of 256 x 256 tiles would leave most
+// of the chip idle (tile = 128 or 64)
+lc_status gemm_tile_launch(GemmP p, const lc_gemm_args &a, int tile, hipStream_t s);
+
+}  // namespace lc

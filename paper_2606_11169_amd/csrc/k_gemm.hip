@@ -61,9 +61,7 @@
 // Output, residual and gate/up element types are run-time values (uniform
 // branches in the epilogue only), except in the instantiations for the decoder
 // stage's own type mix (EpiTypes below), where they are compile-time constants.
-#include "common.hpp"
-
-#include <type_traits>
+#include "gemm_common.hpp"
 
 namespace lc {
 namespace {
@@ -73,79 +71,8 @@ constexpr int KS = 64;             // k per stage
 constexpr int NT = 512;            // threads per workgroup (8 waves)
 constexpr int WM = 64, WN = 128;   // wave tile
 constexpr int FM = WM / 16, FN = WN / 16;  // 16 x 16 MFMA blocks of a wave
-// LDS-DMA runs: one 1 KiB load per wave instruction, 32 bytes of padding after
-// each run.
-constexpr int RUN = 1024 + 32;
 constexpr int OPND_BYTES = 32 * RUN;       // one operand's stage in LDS (32 runs)
 constexpr int STAGE_BYTES = 2 * OPND_BYTES;   // A | B
-constexpr uint32_t OOB = 0x80000000u;    // buffer offset beyond every operand: reads 0
-
-typedef __attribute__((ext_vector_type(4))) short s16x4_v;
-// LDS addresses stay 32-bit LDS-space pointers throughout (no generic pointers)
-typedef __attribute__((address_space(3))) char lds_t;
-typedef __attribute__((address_space(3))) bf16x8_v lds_v8;
-typedef __attribute__((address_space(3))) s16x4_v lds_v4;
-#define LDS_AS(T, ptr) ((__attribute__((address_space(3))) T *)(ptr))
-
-struct GemmP {
-  const bf16_t *A;
-  const bf16_t *B;
-  void *C;
-  const void *R;
-  void *aux0;
-  void *aux1;
-  const float *rcos;
-  const float *rsin;
-  int64_t lda, ldb, ldc, ldr, ld_aux;
-  uint32_t a_bytes, b_bytes;  // byte extent of each operand (< 2^31)
-  int M, N, K;  // N: output columns (SwiGLU: gate/up width)
-  int tiles_m, tiles_n;
-  int group;  // tile-rows per group of the tile walk
-  int gmode, ngroups;
-  const int32_t *goff;
-  int64_t gstride_b, gstride_c;
-  int rope_seq, rope_cols;
-  int c_dt, r_dt, aux_dt;
-};
-
-typedef __attribute__((ext_vector_type(4))) int i32x4_v;
-
-// Raw buffer descriptor (CDNA: dword3 = 0x00020000, stride 0): offsets past
-// `bytes` read as zero.
-__device__ __forceinline__ i32x4_v make_rsrc(const void *base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  i32x4_v r;
-  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-  r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu));
-  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
-  r[3] = 0x00020000;
-  return r;
-}
-
-// 16 bytes per lane from the buffer at byte offset `off` into LDS at
-// lds + 16 * lane. Issued as inline assembly: the compiler then does not track
-// the load, so it inserts no wait for it before LDS reads of the other stage;
-// the step's explicit wait before its barrier is what orders it.
-__device__ __forceinline__ void dma16(i32x4_v rs, lds_t *lds, uint32_t off) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(off), "s"(rs), "s"(m0)
-               : "memory", "m0");
-}
-
-// The same with a wave-uniform part of the offset in the instruction's scalar
-// offset. The hardware checks only the per-lane offset against the buffer's
-// size, so callers use it where every lane's whole offset is inside the
-// operand or the lane's own offset is OOB.
-__device__ __forceinline__ void dma16s(i32x4_v rs, lds_t *lds, uint32_t voff, uint32_t soff) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :
-               : "v"(voff), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(m0)
-               : "memory", "m0");
-}
-
 // One wave's share of an operand's loads: 8 of the 32 1-KiB LDS runs of a
 // 256 x 64 stage (the four waves of a group load one operand).
 //   k-major: run q = tile rows q + 32 p (p = 0..7); lane l -> position l/8,
@@ -247,34 +174,6 @@ __device__ __forceinline__ bf16x8_v frag(const lds_t *t, int row0, int s, int la
   }
 }
 
-// Scheduling pattern for one k-step: the NRD LDS reads of the next k-step
-// spread over the NMF MFMAs of this one (reads first, as evenly as possible).
-template <int NRD, int NMF, int I = 0>
-__device__ __forceinline__ void interleave_steps() {
-  if constexpr (I < NMF) {
-    constexpr int r = NRD / NMF + (I < NRD % NMF ? 1 : 0);
-    if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);  // LDS reads
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
-    interleave_steps<NRD, NMF, I + 1>();
-  }
-}
-
-// Element types of an epilogue's tensors: TM = 0 takes them from the run-time
-// values in GemmP (uniform branches around every access); TM = 1 fixes them to
-// the decoder stage's own mix for EPI (the branch-free accesses let the
-// compiler keep the epilogue's loads in flight instead of waiting at each
-// branch): residual add fp32 R and C, SwiGLU and its backward fp32 gate/up and
-// bf16 C, RoPE fp16 C and bf16 copy. The host takes TM = 1 when the call's
-// types are exactly that mix.
-template <int EPI, int TM>
-struct EpiTypes {
-  static constexpr bool RES = EPI == LC_EPI_RESIDUAL, SWI = EPI == LC_EPI_SWIGLU || EPI == LC_EPI_SWIGLU_BWD;
-  static constexpr bool ROPE = EPI == LC_EPI_ROPE;
-  static constexpr int C = TM == 0 ? -1 : RES ? LC_FP32 : SWI ? LC_BF16 : ROPE ? LC_FP16 : -1;
-  static constexpr int R = TM == 0 ? -1 : RES ? LC_FP32 : -1;
-  static constexpr int X = TM == 0 ? -1 : SWI ? LC_FP32 : ROPE ? LC_BF16 : -1;
-};
-
 template <bool A_K, bool B_K, int EPI, int TM>
 __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   __shared__ __align__(16) char ring[2 * STAGE_BYTES];
@@ -285,48 +184,12 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   const int grp = wave >> 2, w4 = wave & 3;
   const int wm = w4, wn = grp;  // group g owns output columns [128 g, 128 g + 128)
 
-  // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
-  // contiguous run of tiles, then walk tiles in groups of p.group tile-rows
-  // (chosen by the host) so that neighbouring workgroups share A rows
-  // and B columns in the XCD's L2.
-  int wg = blockIdx.x;
-  const int nwg = gridDim.x;
-  if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
   constexpr bool SWI = (EPI == LC_EPI_SWIGLU);
-  int m0, tn, m_lim = p.M, kbeg = 0, kend = p.K;
-  const bf16_t *Bp = p.B;
-  void *Cp = p.C;
-  if (p.gmode == LC_GROUP_ROWS) {
-    // tile slot wg / tiles_n walks the groups' row tiles in order; slots past
-    // the last group's tiles have nothing to do (the grid is an upper bound)
-    tn = wg % p.tiles_n;
-    int slot = wg / p.tiles_n, g = 0, lo = 0, hi = 0;
-    for (; g < p.ngroups; ++g) {
-      lo = min(max(p.goff[g], 0), p.M);
-      hi = min(max(p.goff[g + 1], lo), p.M);
-      const int nt = (hi - lo + BM - 1) / BM;
-      if (slot < nt) break;
-      slot -= nt;
-    }
-    if (g == p.ngroups) return;  // uniform across the workgroup, before any barrier
-    m0 = lo + slot * BM;
-    m_lim = hi;
-    Bp = p.B + (int64_t)g * p.gstride_b;
-  } else {
-    int t = wg;
-    if (p.gmode == LC_GROUP_K) {
-      const int per = p.tiles_m * p.tiles_n, g = t / per;
-      t -= g * per;
-      kbeg = min(max(p.goff[g], 0), p.K);
-      kend = min(max(p.goff[g + 1], kbeg), p.K);
-      Cp = static_cast<char *>(p.C) + (int64_t)g * p.gstride_c * (p.c_dt == LC_FP32 ? 4 : 2);
-    }
-    const int per_group = p.group * p.tiles_n;
-    const int first_m = (t / per_group) * p.group;
-    const int gsz = min(p.tiles_m - first_m, p.group);
-    m0 = (first_m + (t % per_group) % gsz) * BM;
-    tn = (t % per_group) / gsz;
-  }
+  Tile tile;
+  if (!find_tile<BM>(p, tile)) return;  // before any barrier
+  const int m0 = tile.m0, tn = tile.tn, m_lim = tile.m_lim, kbeg = tile.kbeg, kend = tile.kend;
+  const bf16_t *const Bp = tile.B;
+  void *const Cp = tile.C;
   const int n0 = SWI ? tn * (BN / 2) : tn * BN;  // first output column
 
   f32x4_v acc[FM][FN];
@@ -670,6 +533,36 @@ static lc_status check_gemm_args(const lc_gemm_args &a) {
   return LC_OK;
 }
 
+// Output tile of a product: the one whose grid is expected to take the least
+// time per unit of k. One workgroup runs per compute unit with every tile size,
+// so a grid of t tiles takes ceil(t / 256) rounds. Measured ns per k and round
+// (2048 x 2048 to 4096 x 11008 outputs, all compute units busy): 26 with 256 x
+// 256 tiles, 8.5 with 128 x 128, 4.4 with 64 x 64; a 256 x 256 round that fills
+// only part of the chip takes 17.7 + 8.3 x the part. The larger tile does more
+// work per round, the smaller ones fill the chip: 2048 x 2048 outputs (64, 256
+// or 1024 tiles) at K = 5632 take 107, 49 or 103 us; 2048 x 6144 at K = 2048
+// (192, 768 or 3072 tiles) 53, 60 or 135 us; 256 x 512 at K = 1408 (2, 8 or 32
+// tiles) 31, 13 or 9 us. The choice depends on the output's size and the
+// grouping only, so products of the same shape add in the same order whatever
+// their epilogue (an accumulated and a stored gradient are the same bits).
+static int pick_tile(const lc_gemm_args &a) {
+  const int64_t N = a.epilogue == LC_EPI_SWIGLU ? 2 * a.N : a.N;
+  auto tiles = [&](int64_t t) {
+    int64_t tm = (a.M + t - 1) / t;
+    const int64_t tn = (N + t - 1) / t;
+    // grouped rows: about half a partial tile-row per group besides
+    if (a.group_mode == LC_GROUP_ROWS) tm += (a.n_groups + 1) / 2;
+    return tm * tn * (a.group_mode == LC_GROUP_K ? a.n_groups : 1);
+  };
+  constexpr int64_t CU = 256;
+  const int64_t t256 = tiles(256), part = t256 % CU;
+  const int64_t c256 = t256 / CU * 260 + (part ? 177 + 83 * part / CU : 0);
+  const int64_t c128 = (tiles(128) + CU - 1) / CU * 85;
+  const int64_t c64 = (tiles(64) + CU - 1) / CU * 44;
+  if (c64 < c128 && c64 < c256) return 64;
+  return c128 < c256 ? 128 : 256;
+}
+
 lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
   LC_TRY(check_gemm_args(a));
   if (a.dtype == LC_FP32 && a.group_mode != LC_GROUP_NONE)
@@ -738,6 +631,8 @@ lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
   p.r_dt = a.r_dtype;
   p.aux_dt = a.aux_dtype;
 
+  const int tile = pick_tile(a);
+  if (tile != BM) return gemm_tile_launch(p, a, tile, s);
   const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
   switch (a.epilogue) {
     case LC_EPI_STORE:

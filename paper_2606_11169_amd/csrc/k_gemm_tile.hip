@@ -1,0 +1,385 @@
+// bf16 GEMM with 128 x 128 or 64 x 64 output tiles: the products whose grid of
+// 256 x 256 tiles (k_gemm.hip) would leave most of the 256 compute units idle.
+// Same operands, layouts, epilogues and per-element arithmetic.
+//
+// What bounds such a product is not the matrix cores but the serial chain of
+// one tile: with few tiles per compute unit there is no second workgroup to
+// cover a stage's load latency. So k is split inside the workgroup as well:
+// every wave owns a 64 x 64 block of the tile for its own k-step of each stage
+// (the 128 tile: 8 waves = 2 x 2 blocks x 2 k-steps of a 64-deep stage; the 64
+// tile: 4 waves = 4 k-steps of a 128-deep stage), which halves (quarters) the
+// chain, reads no operand row of the 64 tile twice from LDS, and keeps both
+// (one) waves of a SIMD busy; the waves' partial tiles are added in k-step order
+// in the epilogue, through LDS. (At 2048 x 2048 x 11264 the 128 tile runs at 1040
+// TFLOP/s with one tile per compute unit; 64 tiles of 256 x 256 at 473. The 64
+// tile takes 9 us for a 256 x 512 x 1408 product, the 256 tile 31.) Operands stream HBM->LDS through a ring of four
+// stages, three stages ahead of the one being multiplied (the 256 tile's two 64
+// KiB stages leave no room for that; here a stage is 32 KiB), one barrier per
+// stage, the next stage's fragments read while one multiplies.
+#include "gemm_common.hpp"
+
+namespace lc {
+namespace {
+
+constexpr int NST = 4;  // stages of the LDS ring
+
+template <int T> struct Cfg;
+template <> struct Cfg<128> {
+  static constexpr int SUB = 1, WR = 2, KSPL = 2;  // 64-deep slices per stage, waves per side, along k
+};
+template <> struct Cfg<64> {
+  static constexpr int SUB = 2, WR = 1, KSPL = 4;
+};
+
+// What a tile column j of B is: B_PLAIN operand row n0 + j; B_ROPE (64 tile)
+// columns c0 + [0, 32) and 64 + c0 + [0, 32) of one head, so that a rotated
+// pair is in one tile; B_SWIGLU the first half gate rows, the second up rows.
+enum { B_PLAIN, B_ROPE, B_SWIGLU };
+
+// A slice of 64 k of an operand (T rows) in LDS: T / 8 runs of 1 KiB, RUN bytes
+// apart, placed so that the 16 lanes of one phase of a fragment read ({0-3,
+// 12-15} of a chunk, 4-11 of the next, and the like; 32 lanes for the transposing
+// read) touch different banks.
+//   k-major (128-byte rows, eight to a run), row r = 16 f + i:
+//     T = 128: position f of run i
+//     T = 64: position (f & 1) + 2 (i / 8) + 4 (f / 2) of run i % 8
+//   m/n-major (k rows of 2 T bytes), k row k:
+//     T = 128: position k / 16 (of 4) of run swap23(k % 16) (swap23 exchanges
+//       bits 2 and 3)
+//     T = 64: position bit2(k) + 2 bit4(k) + 4 bit5(k) of run (k & 3) + 4 bit3(k)
+template <int T, bool KMAJ>
+struct Opnd {
+  static constexpr int RUNS = T / 8;
+
+  // MFMA operand: rows 16 f .. + 15 at k = 32 s + 8 (lane / 16) + [0, 8)
+  __device__ __forceinline__ static bf16x8_v frag(const lds_t *t, int f, int s, int lane) {
+    if constexpr (KMAJ) {
+      const int i = lane & 15;
+      const lds_t *p = t + (lane >> 4) * 16 + s * 64;
+      if constexpr (T == 128) p += i * RUN + f * 128;
+      else p += (i & 7) * RUN + ((f & 1) + 2 * (i >> 3) + 4 * (f >> 1)) * 128;
+      return *reinterpret_cast<const lds_v8 *>(p);
+    } else {
+      const int i16 = lane & 15, g = lane >> 4;
+      const lds_t *p = t + ((i16 >> 2) + 4 * (g & 1)) * RUN + f * 32 + (i16 & 3) * 8;
+      if constexpr (T == 128) p += ((g >> 1) + 2 * s) * 256;
+      else p += (2 * (g >> 1) + 4 * s) * 128;
+      constexpr int HI = T == 128 ? 8 * RUN : 128;  // k + 4
+      const s16x4_v v[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p)),
+                            __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p + HI))};
+      return __builtin_bit_cast(bf16x8_v, v);
+    }
+  }
+
+  // this lane's part of load run q: its k inside the slice ...
+  __device__ __forceinline__ static int run_k(int q, int lane) {
+    if constexpr (KMAJ) return 8 * (lane & 7);
+    else if constexpr (T == 128) return (q & 3) + 8 * ((q >> 2) & 1) + 4 * (q >> 3) + 16 * (lane >> 4);
+    else {
+      const int pos = lane >> 3;
+      return (q & 3) + 8 * (q >> 2) + 4 * (pos & 1) + 16 * ((pos >> 1) & 1) + 32 * (pos >> 2);
+    }
+  }
+  // ... and its tile row (m/n-major: the first of 8)
+  __device__ __forceinline__ static int run_row(int q, int lane) {
+    if constexpr (!KMAJ) return 8 * (lane & (T / 8 - 1));
+    const int pos = lane >> 3;
+    if constexpr (T == 128) return 16 * pos + q;
+    else return 16 * ((pos & 1) + 2 * (pos >> 2)) + 8 * ((pos >> 1) & 1) + q;
+  }
+
+  // byte offset of that part at k = k0 of the slice's first k (OOB: not in the operand)
+  template <int MAP>
+  __device__ __forceinline__ static uint32_t offset(int q, int lane, int64_t ld, int base, int lim, int k0) {
+    const int j = run_row(q, lane), k = k0 + run_k(q, lane);
+    int row = base + j, chk = row;
+    if constexpr (MAP == B_SWIGLU) {  // base: first output column; lim: gate rows
+      chk = base + (j & (T / 2 - 1));
+      row = j < T / 2 ? chk : lim + chk;
+    } else if constexpr (MAP == B_ROPE && T == 64) {  // base: 64 x tile column
+      row = chk = (base & ~127) + (base & 64) / 2 + (j & 31) + 2 * (j & 32);
+    }
+    if (chk >= lim) return OOB;
+    return KMAJ ? (uint32_t)(((int64_t)row * ld + k) * 2) : (uint32_t)(((int64_t)k * ld + row) * 2);
+  }
+};
+
+// at most LEFT of this wave's loads in flight and its LDS reads done, then the
+// workgroup's barrier
+template <int LEFT>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LEFT) : "memory");
+}
+
+template <int T, bool A_K, bool B_K, int EPI, int TM>
+__global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
+  using C = Cfg<T>;
+  constexpr int NT = T * 4, NW = NT / 64, KS = 64 * C::SUB;
+  constexpr int OPB = (T / 8) * RUN;           // one operand's 64-deep slice
+  constexpr int STAGE = 2 * C::SUB * OPB;      // slices of A | B
+  constexpr int LPW = C::SUB * (T / 8) / (NW / 2);  // loads per wave and stage
+  static_assert(NST * STAGE >= C::KSPL * T * T * 4, "the epilogue's partial tiles reuse the ring");
+  __shared__ __align__(16) char ring[NST * STAGE];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave / (C::WR * C::WR);  // this wave's k-step of a stage
+  const int wr = wave % (C::WR * C::WR) / C::WR, wc = wave % C::WR;
+  constexpr bool SWI = EPI == LC_EPI_SWIGLU;
+  constexpr int MAPB = SWI ? B_SWIGLU : EPI == LC_EPI_ROPE ? B_ROPE : B_PLAIN;
+  Tile tile;
+  if (!find_tile<T>(p, tile)) return;  // before any barrier
+  const int m0 = tile.m0, m_lim = tile.m_lim, kbeg = tile.kbeg, kend = tile.kend;
+  const int n0 = SWI ? tile.tn * (T / 2) : tile.tn * T;
+
+  f32x4_v acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_v{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // the first half of the waves streams A, the second B: runs LPW wo .. + LPW - 1
+  // of the operand's SUB T / 8 runs of a stage
+  lds_t *const R0 = LDS_AS(char, ring);
+  const int ns = (kend - kbeg + KS - 1) / KS;
+  const int grp = wave / (NW / 2), wo = wave % (NW / 2);
+  const i32x4_v rs = grp == 0 ? make_rsrc(p.A, p.a_bytes) : make_rsrc(tile.B, p.b_bytes);
+  uint32_t vo[LPW];
+  const int sub = wo * LPW / (T / 8), q0 = wo * LPW % (T / 8);
+#pragma unroll
+  for (int t = 0; t < LPW; ++t)
+    vo[t] = grp == 0
+                ? Opnd<T, A_K>::template offset<B_PLAIN>(q0 + t, lane, p.lda, m0, m_lim, kbeg + 64 * sub)
+                : Opnd<T, B_K>::template offset<MAPB>(q0 + t, lane, p.ldb, n0, p.N, kbeg + 64 * sub);
+  const bool gk = grp == 0 ? A_K : B_K;
+  const uint32_t kbw = gk ? 2u : (uint32_t)((grp == 0 ? p.lda : p.ldb) * 2);
+  lds_t *const dst0 = R0 + (2 * sub + grp) * OPB + q0 * RUN;
+  const bool ragged = (kend - kbeg) % KS != 0;
+  auto load = [&](int st) {
+    lds_t *d = dst0 + (st & (NST - 1)) * STAGE;
+    const uint32_t so = (uint32_t)(st * KS) * kbw;
+    if (ragged && st == ns - 1) {  // the stage ends past K: every lane checked
+      const int kr = kend - kbeg - st * KS - 64 * sub;  // valid k of this slice
+#pragma unroll
+      for (int t = 0; t < LPW; ++t) {
+        const int k = grp == 0 ? Opnd<T, A_K>::run_k(q0 + t, lane) : Opnd<T, B_K>::run_k(q0 + t, lane);
+        dma16(rs, d + t * RUN, k < kr && vo[t] != OOB ? vo[t] + so : OOB);
+      }
+      return;
+    }
+#pragma unroll
+    for (int t = 0; t < LPW; ++t) dma16s(rs, d + t * RUN, vo[t], so);
+  };
+
+  bf16x8_v fa[2][4], fb[2][4];
+  auto read = [&](int st, bf16x8_v (&a)[4], bf16x8_v (&b)[4]) {
+    const lds_t *t = R0 + (st & (NST - 1)) * STAGE + 2 * (kg >> 1) * OPB;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = Opnd<T, A_K>::frag(t, 4 * wr + i, kg & 1, lane);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = Opnd<T, B_K>::frag(t + OPB, 4 * wc + j, kg & 1, lane);
+  };
+  auto multiply = [&](const bf16x8_v (&a)[4], const bf16x8_v (&b)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+  };
+  constexpr int NRD = (A_K ? 4 : 8) + (B_K ? 4 : 8);
+  // Stage st + 1 has landed for every wave after the barrier, and every wave has
+  // its fragments of stage st, whose slot then takes stage st + NST.
+  auto step = [&](int st, bf16x8_v (&a)[4], bf16x8_v (&b)[4], bf16x8_v (&an)[4], bf16x8_v (&bn)[4]) {
+    const int later = ns - 2 - st;  // stages after st + 1, in flight at most NST - 2
+    if (later >= NST - 2) wait_barrier<(NST - 2) * LPW>();
+    else if (later == 1) wait_barrier<LPW>();
+    else wait_barrier<0>();
+    if (st + NST < ns) load(st + NST);
+    read(st + 1, an, bn);  // (after the last stage: another slot's stale data, unused)
+    multiply(a, b);
+    interleave_steps<NRD, 16>();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(NST == 4, "the waits above");
+#pragma unroll 1
+  for (int st = 0; st < min(ns, NST); ++st) load(st);
+  if (ns >= 4) wait_barrier<3 * LPW>();
+  else if (ns == 3) wait_barrier<2 * LPW>();
+  else if (ns == 2) wait_barrier<LPW>();
+  else wait_barrier<0>();
+  if (ns > 0) read(0, fa[0], fb[0]);
+  for (int st = 0; st < ns; st += 2) {
+    step(st, fa[0], fb[0], fa[1], fb[1]);
+    if (st + 1 < ns) step(st + 1, fa[1], fb[1], fa[0], fb[0]);
+  }
+
+  // ------------------------------------------------------------ epilogue
+  // Every wave writes its partial 64 x 64 block to its k-step's copy of the fp32
+  // tile in the (now idle) ring, 16-byte chunk c of row r at chunk c ^ (r & 15);
+  // then each thread adds the copies of four columns (a pair of fours for RoPE
+  // and SwiGLU) in k-step order and stores them, whole rows by consecutive lanes.
+  // Tensors the epilogue reads are loaded before the barrier.
+  typedef EpiTypes<EPI, TM> ET;
+  const int c_dt = ET::C >= 0 ? ET::C : p.c_dt, r_dt = ET::R >= 0 ? ET::R : p.r_dt,
+            aux_dt = ET::X >= 0 ? ET::X : p.aux_dt;
+  typedef __attribute__((address_space(3))) f32x4_v lds_f4;
+  constexpr bool PAIR = EPI == LC_EPI_ROPE || SWI;
+  constexpr int QW = PAIR ? T / 8 : T / 4;   // column quads a row's threads take
+  constexpr int IT = T * QW / NT;
+  constexpr bool LD = EPI == LC_EPI_RESIDUAL || EPI == LC_EPI_ACCUM_F32 || EPI == LC_EPI_SWIGLU_BWD;
+  const int q = tid % QW;
+  int n;  // first of this thread's columns
+  if constexpr (EPI == LC_EPI_ROPE && T == 64) n = (n0 & ~127) + (n0 & 64) / 2 + 4 * q;
+  else n = n0 + 4 * q;
+  const bool n_ok = n < p.N;
+  auto row_of = [&](int it) { return (it * NT + tid) / QW; };
+  float4 x[IT], y[IT];
+  if constexpr (LD) {
+    const int nc = n_ok ? n : 0;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int64_t mc = min(m0 + row_of(it), m_lim - 1);
+      if constexpr (EPI == LC_EPI_RESIDUAL) x[it] = load4_dt(p.R, mc * p.ldr + nc, r_dt);
+      if constexpr (EPI == LC_EPI_ACCUM_F32)
+        x[it] = *reinterpret_cast<const float4 *>(static_cast<const float *>(tile.C) + mc * p.ldc + nc);
+      if constexpr (EPI == LC_EPI_SWIGLU_BWD) {
+        x[it] = load4_dt(p.aux0, mc * p.ld_aux + nc, aux_dt);
+        y[it] = load4_dt(p.aux1, mc * p.ld_aux + nc, aux_dt);
+      }
+    }
+  }
+  __syncthreads();  // every wave's last fragment reads are done
+  lds_t *const E = R0 + kg * (T * T * 4);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int r = 64 * wr + 16 * i + (lane & 15), c = 16 * wc + 4 * j + (lane >> 4);
+      *reinterpret_cast<lds_f4 *>(E + r * (T * 4) + ((c ^ (r & 15)) << 4)) = acc[i][j];
+    }
+  __syncthreads();
+  auto sum4 = [&](int r, int c) {
+    const lds_t *s = R0 + r * (T * 4) + ((c ^ (r & 15)) << 4);
+    f32x4_v v = *reinterpret_cast<const lds_f4 *>(s);
+#pragma unroll
+    for (int k = 1; k < C::KSPL; ++k) v += *reinterpret_cast<const lds_f4 *>(s + k * (T * T * 4));
+    return v;
+  };
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int r = row_of(it), m = m0 + r;
+    if (m >= m_lim || !n_ok) continue;
+    const f32x4_v v = sum4(r, q);
+    const int64_t oc = (int64_t)m * p.ldc + n;
+    if constexpr (PAIR) {
+      const f32x4_v w = sum4(r, q + QW);
+      float a[4] = {v[0], v[1], v[2], v[3]}, b[4] = {w[0], w[1], w[2], w[3]};
+      if constexpr (EPI == LC_EPI_ROPE) {
+        if (n < p.rope_cols) {
+          const int64_t ta = (int64_t)(m % p.rope_seq) * 64 + (n & 127);
+          const float4 cs = *reinterpret_cast<const float4 *>(p.rcos + ta);
+          const float4 sn = *reinterpret_cast<const float4 *>(p.rsin + ta);
+          const float cv[4] = {cs.x, cs.y, cs.z, cs.w}, sv[4] = {sn.x, sn.y, sn.z, sn.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float xx = a[e], yy = b[e];
+            a[e] = xx * cv[e] - yy * sv[e];
+            b[e] = xx * sv[e] + yy * cv[e];
+          }
+        }
+        store4_dt(tile.C, oc, c_dt, a[0], a[1], a[2], a[3]);
+        store4_dt(tile.C, oc + 64, c_dt, b[0], b[1], b[2], b[3]);
+        if (p.aux0) {  // a second copy in aux_dt
+          const int64_t oa = (int64_t)m * p.ld_aux + n;
+          store4_dt(p.aux0, oa, aux_dt, a[0], a[1], a[2], a[3]);
+          store4_dt(p.aux0, oa + 64, aux_dt, b[0], b[1], b[2], b[3]);
+        }
+      } else {
+        float act[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) act[e] = a[e] * sigmoidf_(a[e]) * b[e];
+        const int64_t oa = (int64_t)m * p.ld_aux + n;
+        store4_dt(p.aux0, oa, aux_dt, a[0], a[1], a[2], a[3]);
+        store4_dt(p.aux1, oa, aux_dt, b[0], b[1], b[2], b[3]);
+        store4_dt(tile.C, oc, c_dt, act[0], act[1], act[2], act[3]);
+      }
+    } else if constexpr (EPI == LC_EPI_SWIGLU_BWD) {
+      const float gv[4] = {x[it].x, x[it].y, x[it].z, x[it].w};
+      const float uv[4] = {y[it].x, y[it].y, y[it].z, y[it].w};
+      float dg[4], du[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float sg = sigmoidf_(gv[e]);
+        dg[e] = v[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));
+        du[e] = v[e] * gv[e] * sg;
+      }
+      store4_dt(tile.C, oc, c_dt, dg[0], dg[1], dg[2], dg[3]);
+      store4_dt(tile.C, oc + p.N, c_dt, du[0], du[1], du[2], du[3]);
+    } else if constexpr (EPI == LC_EPI_ACCUM_F32) {
+      *reinterpret_cast<float4 *>(static_cast<float *>(tile.C) + oc) =
+          make_float4(x[it].x + v[0], x[it].y + v[1], x[it].z + v[2], x[it].w + v[3]);
+    } else if constexpr (EPI == LC_EPI_RESIDUAL) {
+      store4_dt(tile.C, oc, c_dt, x[it].x + v[0], x[it].y + v[1], x[it].z + v[2], x[it].w + v[3]);
+    } else {
+      store4_dt(tile.C, oc, c_dt, v[0], v[1], v[2], v[3]);
+    }
+  }
+}
+
+template <bool A_K, bool B_K, int EPI, int TM = 0>
+lc_status launch_t(const GemmP &p, int tile, hipStream_t s) {
+  unsigned grid = (unsigned)p.tiles_m * (unsigned)p.tiles_n;
+  if (p.gmode == LC_GROUP_ROWS) grid = (unsigned)(p.tiles_m + p.ngroups) * (unsigned)p.tiles_n;
+  if (p.gmode == LC_GROUP_K) grid *= (unsigned)p.ngroups;
+  if (tile == 128)
+    hipLaunchKernelGGL((gemm_tile_kernel<128, A_K, B_K, EPI, TM>), dim3(grid), dim3(512), 0, s, p);
+  else
+    hipLaunchKernelGGL((gemm_tile_kernel<64, A_K, B_K, EPI, TM>), dim3(grid), dim3(256), 0, s, p);
+  return check_launch("gemm_tile_kernel");
+}
+
+}  // namespace
+
+lc_status gemm_tile_launch(GemmP p, const lc_gemm_args &a, int tile, hipStream_t s) {
+  const int cols = a.epilogue == LC_EPI_SWIGLU ? tile / 2 : tile;
+  p.tiles_m = (p.M + tile - 1) / tile;
+  p.tiles_n = (p.N + cols - 1) / cols;
+  const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
+  switch (a.epilogue) {
+    case LC_EPI_STORE:
+    case LC_EPI_STORE_F32:
+      if (ak && bk) return launch_t<true, true, LC_EPI_STORE>(p, tile, s);
+      if (ak && !bk) return launch_t<true, false, LC_EPI_STORE>(p, tile, s);
+      if (!ak && !bk) return launch_t<false, false, LC_EPI_STORE>(p, tile, s);
+      break;
+    case LC_EPI_ACCUM_F32:
+      if (ak && bk) return launch_t<true, true, LC_EPI_ACCUM_F32>(p, tile, s);
+      if (!ak && !bk) return launch_t<false, false, LC_EPI_ACCUM_F32>(p, tile, s);
+      break;
+    case LC_EPI_RESIDUAL:
+      if (ak && bk && p.c_dt == LC_FP32 && p.r_dt == LC_FP32)
+        return launch_t<true, true, LC_EPI_RESIDUAL, 1>(p, tile, s);
+      if (ak && bk) return launch_t<true, true, LC_EPI_RESIDUAL>(p, tile, s);
+      break;
+    case LC_EPI_ROPE:
+      if (ak && bk && p.c_dt == LC_FP16 && (!p.aux0 || p.aux_dt == LC_BF16))
+        return launch_t<true, true, LC_EPI_ROPE, 1>(p, tile, s);
+      if (ak && bk) return launch_t<true, true, LC_EPI_ROPE>(p, tile, s);
+      break;
+    case LC_EPI_SWIGLU:
+      if (ak && bk && p.c_dt == LC_BF16 && p.aux_dt == LC_FP32)
+        return launch_t<true, true, LC_EPI_SWIGLU, 1>(p, tile, s);
+      if (ak && bk) return launch_t<true, true, LC_EPI_SWIGLU>(p, tile, s);
+      break;
+    case LC_EPI_SWIGLU_BWD:
+      if (ak && !bk && p.c_dt == LC_BF16 && p.aux_dt == LC_FP32)
+        return launch_t<true, false, LC_EPI_SWIGLU_BWD, 1>(p, tile, s);
+      if (ak && !bk) return launch_t<true, false, LC_EPI_SWIGLU_BWD>(p, tile, s);
+      if (ak && bk) return launch_t<true, true, LC_EPI_SWIGLU_BWD>(p, tile, s);
+      break;
+  }
+  return fail(LC_ERR_UNSUPPORTED, "gemm bf16: layout (a_kmajor=%d, b_kmajor=%d) not built for "
+              "epilogue %d", (int)ak, (int)bk, a.epilogue);
+}
+
+}  // namespace lc
