@@ -151,6 +151,9 @@ lc_status qknorm_dg_final_launch(const float *partial, float *dgq, float *dgk, i
                                  bool store, hipStream_t s);
 lc_status attn_fwd_launch(const lc_attn_args &a, hipStream_t s);
 lc_status attn_bwd_launch(const lc_attn_args &a, hipStream_t s);
+// the fp32 path of the two above (arguments already checked)
+lc_status attn_f32_fwd_launch(const lc_attn_args &a, hipStream_t s);
+lc_status attn_f32_bwd_launch(const lc_attn_args &a, hipStream_t s);
 lc_status accumulate_launch(float *acc, const void *g, int g_dtype, size_t n, hipStream_t s);
 lc_status adam_launch(float *p, float *m, float *v, const void *g, int g_dtype, uint16_t *out,
                       size_t n, const lc_adam_hparams &hp, hipStream_t s);

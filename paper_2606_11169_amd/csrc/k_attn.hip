@@ -1,5 +1,5 @@
 // Causal softmax attention on CDNA4 matrix cores (head_dim 128, fp16 or bf16
-// q/k/v operands, fp32 softmax and accumulation), plus a plain fp32 path.
+// q/k/v operands, fp32 softmax and accumulation). The fp32 path is k_attn_f32.hip.
 //
 // Forward (written from the FlashAttention-2 algorithm of Dao, 2023): a
 // workgroup of 8 waves owns 256 queries of one (batch row, head); each wave
@@ -849,134 +849,7 @@ __global__ __launch_bounds__(256) void attn_gqa_sum_kernel(AttnP p) {
   }
 }
 
-// ---------------------------------------------------------------- fp32 path
-// Plain kernels: one thread per (batch row, head, query) or (..., key).
-struct AttnF {
-  const float *q, *k, *v;
-  float *o;
-  float *lse;
-  const float *dout;
-  float *dq, *dk, *dv;
-  float *D;
-  const float *rcos, *rsin;
-  int64_t ld_qkv, ld_o, ld_d;
-  int B, S, H, hd;
-  int Hkv, G;  // key/value heads; query heads per key/value head
-  float scale;
-};
-
-constexpr int MAXHD = 128;
-
-__global__ void attn_fwd_f32_kernel(AttnF p) {
-  const int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (id >= (int64_t)p.B * p.H * p.S) return;
-  const int i = (int)(id % p.S), h = (int)((id / p.S) % p.H), b = (int)(id / ((int64_t)p.S * p.H));
-  const int64_t r0 = (int64_t)b * p.S;
-  const float *qi = p.q + (r0 + i) * p.ld_qkv + h * p.hd;
-  const int kvh = h / p.G;
-  float acc[MAXHD];
-  for (int e = 0; e < p.hd; ++e) acc[e] = 0.0f;
-  float m = -INFINITY, l = 0.0f;
-  for (int j = 0; j <= i; ++j) {
-    const float *kj = p.k + (r0 + j) * p.ld_qkv + kvh * p.hd;
-    float s = 0.0f;
-    for (int e = 0; e < p.hd; ++e) s += qi[e] * kj[e];
-    s *= p.scale;
-    const float mn = fmaxf(m, s);
-    const float a = expf(m - mn), w = expf(s - mn);
-    l = l * a + w;
-    const float *vj = p.v + (r0 + j) * p.ld_qkv + kvh * p.hd;
-    for (int e = 0; e < p.hd; ++e) acc[e] = acc[e] * a + w * vj[e];
-    m = mn;
-  }
-  float *oi = p.o + (r0 + i) * p.ld_o + h * p.hd;
-  for (int e = 0; e < p.hd; ++e) oi[e] = acc[e] / l;
-  p.lse[((int64_t)b * p.H + h) * p.S + i] = m + logf(l);
-}
-
-__device__ void rope_inv_vec(float *x, int hd, int pos, const float *rc, const float *rs) {
-  const int half = hd / 2;
-  for (int e = 0; e < half; ++e) {
-    const float c = rc[pos * half + e], s = rs[pos * half + e];
-    const float a = x[e], bb = x[e + half];
-    x[e] = a * c + bb * s;
-    x[e + half] = bb * c - a * s;
-  }
-}
-
-// per query: D_i and dq_i
-__global__ void attn_bwd_q_f32_kernel(AttnF p) {
-  const int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (id >= (int64_t)p.B * p.H * p.S) return;
-  const int i = (int)(id % p.S), h = (int)((id / p.S) % p.H), b = (int)(id / ((int64_t)p.S * p.H));
-  const int64_t r0 = (int64_t)b * p.S;
-  const float *qi = p.q + (r0 + i) * p.ld_qkv + h * p.hd;
-  const float *doi = p.dout + (r0 + i) * p.ld_o + h * p.hd;
-  const float *oi = p.o + (r0 + i) * p.ld_o + h * p.hd;
-  float Di = 0.0f;
-  for (int e = 0; e < p.hd; ++e) Di += doi[e] * oi[e];
-  const int64_t si = ((int64_t)b * p.H + h) * p.S + i;
-  p.D[si] = Di;
-  const float L = p.lse[si];
-  const int kvh = h / p.G;
-  float acc[MAXHD];
-  for (int e = 0; e < p.hd; ++e) acc[e] = 0.0f;
-  for (int j = 0; j <= i; ++j) {
-    const float *kj = p.k + (r0 + j) * p.ld_qkv + kvh * p.hd;
-    const float *vj = p.v + (r0 + j) * p.ld_qkv + kvh * p.hd;
-    float s = 0.0f, dp = 0.0f;
-    for (int e = 0; e < p.hd; ++e) {
-      s += qi[e] * kj[e];
-      dp += doi[e] * vj[e];
-    }
-    const float P = expf(s * p.scale - L);
-    const float dS = P * (dp - Di);
-    for (int e = 0; e < p.hd; ++e) acc[e] += dS * kj[e];
-  }
-  for (int e = 0; e < p.hd; ++e) acc[e] *= p.scale;
-  if (p.rcos) rope_inv_vec(acc, p.hd, i, p.rcos, p.rsin);
-  float *dqi = p.dq + (r0 + i) * p.ld_d + h * p.hd;
-  for (int e = 0; e < p.hd; ++e) dqi[e] = acc[e];
-}
-
-// per key and key/value head: dk_j and dv_j summed over the head's query
-// heads in order (needs D from the kernel above)
-__global__ void attn_bwd_kv_f32_kernel(AttnF p) {
-  const int64_t id = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (id >= (int64_t)p.B * p.Hkv * p.S) return;
-  const int j = (int)(id % p.S), kvh = (int)((id / p.S) % p.Hkv);
-  const int b = (int)(id / ((int64_t)p.S * p.Hkv));
-  const int64_t r0 = (int64_t)b * p.S;
-  const float *kj = p.k + (r0 + j) * p.ld_qkv + kvh * p.hd;
-  const float *vj = p.v + (r0 + j) * p.ld_qkv + kvh * p.hd;
-  float ak[MAXHD], av[MAXHD];
-  for (int e = 0; e < p.hd; ++e) ak[e] = av[e] = 0.0f;
-  for (int h = kvh * p.G; h < (kvh + 1) * p.G; ++h)
-  for (int i = j; i < p.S; ++i) {
-    const float *qi = p.q + (r0 + i) * p.ld_qkv + h * p.hd;
-    const float *doi = p.dout + (r0 + i) * p.ld_o + h * p.hd;
-    float s = 0.0f, dp = 0.0f;
-    for (int e = 0; e < p.hd; ++e) {
-      s += qi[e] * kj[e];
-      dp += doi[e] * vj[e];
-    }
-    const int64_t si = ((int64_t)b * p.H + h) * p.S + i;
-    const float P = expf(s * p.scale - p.lse[si]);
-    const float dS = P * (dp - p.D[si]);
-    for (int e = 0; e < p.hd; ++e) {
-      av[e] += P * doi[e];
-      ak[e] += dS * qi[e];
-    }
-  }
-  for (int e = 0; e < p.hd; ++e) ak[e] *= p.scale;
-  if (p.rcos) rope_inv_vec(ak, p.hd, j, p.rcos, p.rsin);
-  float *dkj = p.dk + (r0 + j) * p.ld_d + kvh * p.hd;
-  float *dvj = p.dv + (r0 + j) * p.ld_d + kvh * p.hd;
-  for (int e = 0; e < p.hd; ++e) {
-    dkj[e] = ak[e];
-    dvj[e] = av[e];
-  }
-}
+constexpr int MAXHD = 128;  // fp32 path (k_attn_f32.hip)
 
 int kv_of(const lc_attn_args &a) { return a.Hkv > 0 ? a.Hkv : a.H; }
 size_t attn_scratch_bytes_of(const lc_attn_args &a) {
@@ -1103,30 +976,6 @@ lc_status check_extents(const lc_attn_args &a) {
   return LC_OK;
 }
 
-AttnF f32_params(const lc_attn_args &a) {
-  AttnF p{};
-  p.q = static_cast<const float *>(a.q);
-  p.k = static_cast<const float *>(a.k);
-  p.v = static_cast<const float *>(a.v);
-  p.o = static_cast<float *>(a.o);
-  p.lse = a.lse;
-  p.dout = static_cast<const float *>(a.dout);
-  p.dq = static_cast<float *>(a.dq);
-  p.dk = static_cast<float *>(a.dk);
-  p.dv = static_cast<float *>(a.dv);
-  p.D = static_cast<float *>(a.scratch);
-  p.rcos = a.rope_cos;
-  p.rsin = a.rope_sin;
-  p.ld_qkv = a.ld_qkv;
-  p.ld_o = a.ld_o;
-  p.ld_d = a.ld_dqkv;
-  p.B = a.B; p.S = a.S; p.H = a.H; p.hd = a.hd;
-  p.Hkv = kv_of(a);
-  p.G = a.H / p.Hkv;
-  p.scale = 1.0f / sqrtf((float)a.hd);
-  return p;
-}
-
 template <typename QE>
 lc_status fwd_mc(const lc_attn_args &a, hipStream_t s) {
   LC_TRY(check_extents(a));
@@ -1166,24 +1015,14 @@ lc_status attn_fwd_launch(const lc_attn_args &a, hipStream_t s) {
   LC_TRY(check_common(a, false));
   if (a.dtype == LC_FP16) return fwd_mc<_Float16>(a, s);
   if (a.dtype == LC_BF16) return fwd_mc<__bf16>(a, s);
-  const AttnF p = f32_params(a);
-  const int64_t n = (int64_t)a.B * a.H * a.S;
-  hipLaunchKernelGGL(attn_fwd_f32_kernel, dim3((unsigned)((n + 127) / 128)), dim3(128), 0, s, p);
-  return check_launch("attn_fwd_f32_kernel");
+  return attn_f32_fwd_launch(a, s);
 }
 
 lc_status attn_bwd_launch(const lc_attn_args &a, hipStream_t s) {
   LC_TRY(check_common(a, true));
   if (a.dtype == LC_FP16) return bwd_mc<_Float16>(a, s);
   if (a.dtype == LC_BF16) return bwd_mc<__bf16>(a, s);
-  const AttnF p = f32_params(a);
-  const int64_t n = (int64_t)a.B * a.H * a.S;
-  const dim3 grid((unsigned)((n + 127) / 128));
-  hipLaunchKernelGGL(attn_bwd_q_f32_kernel, grid, dim3(128), 0, s, p);
-  LC_TRY(check_launch("attn_bwd_q_f32_kernel"));
-  const int64_t nkv = (int64_t)a.B * p.Hkv * a.S;
-  hipLaunchKernelGGL(attn_bwd_kv_f32_kernel, dim3((unsigned)((nkv + 127) / 128)), dim3(128), 0, s, p);
-  return check_launch("attn_bwd_kv_f32_kernel");
+  return attn_f32_bwd_launch(a, s);
 }
 
 }  // namespace lc

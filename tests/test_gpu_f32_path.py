@@ -1,0 +1,165 @@
+"""The fp32 path's matrix-instruction kernels at the edges of their tiles and
+blocks, against float64: products in every layout and epilogue with rows that are
+and are not whole 16-byte runs, attention over sequence lengths and head sizes
+around the 16-row and 32-key blocks, and values that are not finite."""
+import math
+
+import pytest
+import torch
+
+from paper_2606_11169_amd import libchunk as lc
+from tests.gpu_util import DEV, banner
+
+pytestmark = pytest.mark.gpu
+F32 = lc.LC_FP32
+
+
+def gen(seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return g
+
+
+def close(got, ref, tol):
+    """2-norm relative error; fp32 sums of K N(0, 1) products round to about
+    2^-24 sqrt(K) / sqrt(K) each: a few 1e-7."""
+    e = float((got.double() - ref).norm() / ref.norm().clamp_min(1e-300))
+    assert e < tol, e
+
+
+@pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (33, 31, 5, 0), (130, 66, 129, 3), (128, 344, 128, 0),
+                                       (900, 970, 70, 0), (1030, 1024, 164, 4)])
+@pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 1), (0, 0)])
+def test_products(M, N, K, pad, layout):
+    ak, bk = layout
+    banner(f"gemm f32 {M}x{N}x{K} pad {pad} {layout}")
+    g = gen(M + N + K)
+    A = torch.randn((M, K + pad) if ak else (K, M + pad), generator=g, device=DEV)
+    B = torch.randn((N, K + pad) if bk else (K, N + pad), generator=g, device=DEV)
+    a = A[:, :K] if ak else A[:, :M].t()
+    b = B[:, :K] if bk else B[:, :N].t()
+    ref = a.double() @ b.double().t()
+    C0 = torch.randn((M, N + 1), generator=g, device=DEV)
+    R = torch.randn((M, N), generator=g, device=DEV)
+    for epi, want in ((lc.LC_EPI_STORE, ref), (lc.LC_EPI_ACCUM_F32, C0[:, :N].double() + ref),
+                      (lc.LC_EPI_RESIDUAL, R.double() + ref)):
+        C = C0.clone()
+        lc.lc_gemm(F32, epi, M, N, K, A, A.shape[1], ak, B, B.shape[1], bk, C, N + 1, R=R, ldr=N)
+        close(C[:, :N], want, 1e-6)
+        assert torch.equal(C[:, N], C0[:, N])
+    gate, up = (torch.randn((M, N), generator=g, device=DEV) for _ in range(2))
+    C = torch.empty((M, 2 * N), device=DEV)
+    lc.lc_gemm(F32, lc.LC_EPI_SWIGLU_BWD, M, N, K, A, A.shape[1], ak, B, B.shape[1], bk, C, 2 * N,
+               aux0=gate, aux1=up, ld_aux=N)
+    s = torch.sigmoid(gate.double())
+    close(C[:, :N], ref * up.double() * s * (1 + gate.double() * (1 - s)), 1e-6)
+    close(C[:, N:], ref * gate.double() * s, 1e-6)
+
+
+@pytest.mark.parametrize("T,f,d", [(5, 3, 7), (128, 344, 128), (400, 1500, 36)])
+def test_gate_up(T, f, d):
+    banner(f"gemm f32 swiglu {T} {f} {d}")
+    g = gen(T)
+    x, w = torch.randn((T, d), generator=g, device=DEV), torch.randn((2 * f, d), generator=g, device=DEV)
+    gate, up, act = (torch.empty((T, f), device=DEV) for _ in range(3))
+    lc.lc_gemm(F32, lc.LC_EPI_SWIGLU, T, f, d, x, d, 1, w, d, 1, act, f, aux0=gate, aux1=up, ld_aux=f)
+    gr, ur = x.double() @ w[:f].double().t(), x.double() @ w[f:].double().t()
+    close(gate, gr, 1e-6)
+    close(up, ur, 1e-6)
+    close(act, gr * torch.sigmoid(gr) * ur, 1e-6)
+
+
+@pytest.mark.parametrize("T,H,hd,seq", [(7, 1, 2, 3), (128, 4, 32, 64), (400, 12, 64, 200), (50, 3, 10, 50)])
+def test_rope(T, H, hd, seq):
+    banner(f"gemm f32 rope {T} {H} {hd}")
+    g = gen(T)
+    N, d = 3 * H * hd, H * hd
+    x, w = torch.randn((T, d), generator=g, device=DEV), torch.randn((N, d), generator=g, device=DEV)
+    ang = torch.rand((seq, hd // 2), generator=g, device=DEV)
+    cos, sin = torch.cos(ang), torch.sin(ang)
+    C = torch.empty((T, N), device=DEV)
+    lc.lc_gemm(F32, lc.LC_EPI_ROPE, T, N, d, x, d, 1, w, d, 1, C, N, rope_cos=cos, rope_sin=sin,
+               rope_seq=seq, rope_cols=2 * d, head_dim=hd)
+    ref = (x.double() @ w.double().t()).view(T, 3 * H, hd)
+    pos = torch.arange(T, device=DEV) % seq
+    c, s = cos.double()[pos, None], sin.double()[pos, None]
+    a, b = ref[:, :2 * H, :hd // 2].clone(), ref[:, :2 * H, hd // 2:].clone()
+    ref[:, :2 * H, :hd // 2], ref[:, :2 * H, hd // 2:] = a * c - b * s, a * s + b * c
+    close(C.view(T, 3 * H, hd), ref, 1e-6)
+
+
+def attention(B, S, H, kv, hd, pad, rope, seed=0, poison=None):
+    """(o, lse, dq, dk, dv) of the library and of float64."""
+    g = gen(seed + S + hd)
+    ld = (H + 2 * kv) * hd + pad
+    qkv = torch.randn((B * S, ld), generator=g, device=DEV)
+    dout = torch.randn((B * S, H * hd), generator=g, device=DEV)
+    if poison:
+        poison(qkv, dout)
+    ang = torch.rand((S, hd // 2), generator=g, device=DEV)
+    cos, sin = torch.cos(ang), torch.sin(ang)
+    o, lse = torch.empty_like(dout), torch.empty((B, H, S), device=DEV)
+    q = qkv.data_ptr()
+    k, v = q + 4 * H * hd, q + 4 * (H + kv) * hd
+    lc.lc_attention_forward(F32, F32, B, S, H, hd, q, k, v, ld, o, H * hd, lse, Hkv=kv)
+    d = torch.zeros_like(qkv)
+    dq = d.data_ptr()
+    nb = lc.lc_attention_scratch_bytes(B, S, H, kv)
+    scratch = torch.empty(nb, dtype=torch.uint8, device=DEV)
+    lc.lc_attention_backward(F32, F32, B, S, H, hd, q, k, v, ld, o, dout, H * hd, lse, dq,
+                             dq + 4 * H * hd, dq + 4 * (H + kv) * hd, ld, cos if rope else None,
+                             sin if rope else None, scratch, nb, Hkv=kv)
+    x = qkv[:, :ld - pad].double().view(B, S, H + 2 * kv, hd).requires_grad_()
+    qh, kh, vh = x[:, :, :H], x[:, :, H:H + kv], x[:, :, H + kv:]
+    kh, vh = (t.repeat_interleave(H // kv, 2) for t in (kh, vh))
+    sc = torch.einsum("bqhe,bkhe->bhqk", qh, kh) / math.sqrt(hd)
+    sc = sc.masked_fill(torch.ones((S, S), dtype=torch.bool, device=DEV).triu(1), -math.inf)
+    oh = torch.einsum("bhqk,bkhe->bqhe", torch.softmax(sc, -1), vh)
+    oh.backward(dout.double().view(B, S, H, hd))
+    gr = x.grad
+    if rope:
+        c, s = cos.double()[:, None], sin.double()[:, None]
+        a, b = gr[:, :, :H + kv, :hd // 2].clone(), gr[:, :, :H + kv, hd // 2:].clone()
+        gr[:, :, :H + kv, :hd // 2], gr[:, :, :H + kv, hd // 2:] = a * c + b * s, b * c - a * s
+    return (o, lse, d[:, :ld - pad]), (oh.detach().reshape(B * S, -1), torch.logsumexp(sc, -1).detach(),
+                                       gr.reshape(B * S, -1))
+
+
+@pytest.mark.parametrize("B,S,H,kv,hd,pad,rope", [
+    (1, 1, 2, 2, 2, 0, True), (2, 15, 2, 1, 16, 0, True), (1, 33, 4, 2, 10, 1, True),
+    (2, 64, 4, 4, 32, 0, True), (2, 200, 6, 2, 64, 4, True), (1, 130, 2, 2, 36, 0, False),
+    (1, 300, 2, 1, 128, 0, True), (1, 129, 1, 1, 80, 2, True)])
+def test_attention(B, S, H, kv, hd, pad, rope):
+    banner(f"attention f32 B={B} S={S} H={H}/{kv} hd={hd} pad={pad}")
+    got, ref = attention(B, S, H, kv, hd, pad, rope)
+    for a, b in zip(got, ref):
+        if S > 1 or float(b.abs().max()) > 0:
+            close(a, b, 3e-6)
+
+
+@pytest.mark.parametrize("bad", [math.nan, math.inf])
+def test_values_not_finite_reach_only_who_sees_them(bad):
+    """One value of V and of dO at position 40 of 70 that is not finite: outputs
+    before 40 (o, dq) and, for dO, keys after 40 keep their values, as pair by pair
+    sums would. A block with such a value adds its terms in another order: at most 70
+    terms, so a difference of at most 70 x 2^-24 of the terms' magnitudes, 1e-6 in
+    the 2-norm with the usual partial cancellation of rounding."""
+    banner(f"attention f32 with {bad}")
+    S, H, hd, at = 70, 1, 16, 40
+    (o0, _, d0), _ = attention(1, S, H, H, hd, 0, False, seed=5)
+
+    def in_v(qkv, dout):
+        qkv[at, 2 * hd + 3] = bad
+
+    (o, _, _), _ = attention(1, S, H, H, hd, 0, False, seed=5, poison=in_v)
+    close(o[:at], o0[:at].double(), 1e-6)
+    assert not bool(torch.isfinite(o[at:, 3]).any())
+    close(o[at:, :3], o0[at:, :3].double(), 1e-6)
+
+    def in_do(qkv, dout):
+        dout[at, 3] = bad
+
+    (_, _, d), _ = attention(1, S, H, H, hd, 0, False, seed=5, poison=in_do)
+    close(d[at + 1:, hd:], d0[at + 1:, hd:].double(), 1e-6)  # keys that query 40 does not see
+    assert not bool(torch.isfinite(d[:at + 1, 2 * hd + 3]).any())
+    close(d[:at, :hd], d0[:at, :hd].double(), 1e-6)          # dq of other queries
