@@ -8,12 +8,12 @@
 // Forward: one wave per row, 8 elements per lane per step (16- or 32-byte
 // accesses); rows of up to 4096 elements stay in registers between the row's
 // reduction and its write (one read), longer rows are read twice (the second
-// read hits L2). Backward: rows of up to 4096 elements are split over four
-// waves (so that a workgroup of 16 waves keeps four rows in registers at
-// once and the chip holds enough waves to cover memory latency); longer rows
-// go one per wave, read twice. Every tensor's element type is a run-time
-// value (uniform branches), except in the instantiations for the decoder
-// stage's own type mix, where the types are template arguments (straight-line
+// read hits L2). Backward: rows of up to 8192 elements stay in registers, split
+// over one to eight waves by their length; longer rows go one per wave, read
+// twice (3001 rows of 5120: 134 us that way with its own partial-sum pass, 67 in
+// registers). Every tensor's element type is a run-time
+// value (uniform branches), except in the instantiations for the stages' own
+// type mixes, where the types are template arguments (straight-line
 // loads: 20-25% faster forward, 9% faster backward rows). The gain gradient is a column reduction over
 // rows: each backward workgroup handles kNormRowsPerBlock rows and writes
 // the fp32 partial sums of its rows in a fixed order, then the final kernel
@@ -29,7 +29,8 @@ namespace {
 
 constexpr int ROWS_PER_BLOCK = 4;  // forward: one wave per row
 constexpr int MAXU = 8;            // 8-element chunks per lane held in registers
-constexpr int MAXD = 64 * 8 * MAXU;
+constexpr int MAXD = 64 * 8 * MAXU;  // longest row the forward keeps in registers
+constexpr int MAXB = 8192;           // longest row the backward keeps in registers
 
 struct NormP {
   const void *x, *g, *dn, *dres;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormP p) {
   }
 }
 
-// rows longer than MAXD: the row is read twice, the gain gradient is not formed here
+// rows longer than MAXB: the row is read twice, the gain gradient is not formed here
 __device__ __forceinline__ void bwd_row_long(const NormP &p, int64_t row, int lane) {
   const int64_t base = row * p.d;
   const float r = p.rstd[row];
@@ -132,40 +133,46 @@ __device__ __forceinline__ void bwd_row_long(const NormP &p, int64_t row, int la
   }
 }
 
-// Rows of up to MAXD values: one workgroup of 16 waves per kNormRowsPerBlock
-// rows, 4 waves per row (lane l of wave w of a row holds the 8-value chunks
-// starting at 8 (64 w + l) and 8 (64 w + l) + 2048), four rows at a time:
-// iteration i takes rows 4 i + s (s = wave / 4). A row's dot product is the
-// sum of its four waves' shares in wave order (through LDS); the gain
-// gradient's partial sums: each lane's rows in order, then the four row
-// slots in order, into partial[blk][k].
+// Rows of up to MAXB values: one workgroup of 16 waves per kNormRowsPerBlock
+// rows, WPR waves per row (lane l of wave w of a row holds the U 8-value chunks
+// starting at 8 (64 w + l) + 512 WPR u), 16 / WPR rows at a time: iteration i
+// takes rows 16 / WPR i + s (s = wave / WPR). A row's dot product is the sum of
+// its waves' shares in wave order (through LDS); the gain gradient's partial
+// sums: each lane's rows in order, then the row slots in order, into
+// partial[blk][k].
+//
+// A workgroup's chain of loads and reductions is one iteration long per 16 / WPR
+// rows, so a row gets as few waves as hold it: one up to 512 values (all sixteen
+// rows at once; with four waves per row whatever its length, 128 rows of 128
+// took 12 us, with one and the slots added in one step 4), then WPR = 2, 4 with one chunk per lane, 4 and 8 with two (16
+// values per lane of each tensor, so that four waves per SIMD stay resident).
 constexpr int BW_THREADS = 1024;
-constexpr int BW_CHUNKS = MAXD / 2048;  // 8-value chunks per lane
-template <int DNDT, int XDT, int WDT, int RDT, int ODT>
+template <int WPR, int U, int DNDT, int XDT, int WDT, int RDT, int ODT>
 __global__ __launch_bounds__(BW_THREADS) void rmsnorm_bwd_rows_kernel(NormP p) {
-  __shared__ float red[MAXD];
-  __shared__ float dots[2][4][4];  // [iteration parity][row slot][wave of the row]
+  constexpr int SLOTS = 16 / WPR, SPAN = 512 * WPR;
+  __shared__ __align__(16) float red[SLOTS][SPAN * U];  // (32 or 64 KiB)
+  __shared__ float dots[2][SLOTS][WPR];  // [iteration parity][row slot][wave of the row]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int slot = wv >> 2, wr = wv & 3;
+  const int slot = wv / WPR, wr = wv % WPR;
   const int rl = wr * 64 + lane;
   const int64_t r0 = (int64_t)blockIdx.x * kNormRowsPerBlock;
   const int64_t r1 = min(p.rows, r0 + kNormRowsPerBlock);
-  float acc[BW_CHUNKS][8];
+  float acc[U][8];
 #pragma unroll
-  for (int u = 0; u < BW_CHUNKS; ++u)
+  for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[u][e] = 0.0f;
 #pragma unroll 1
-  for (int i = 0; i < kNormRowsPerBlock / 4; ++i) {
-    const int64_t row = r0 + 4 * i + slot;
+  for (int i = 0; i < kNormRowsPerBlock / SLOTS; ++i) {
+    const int64_t row = r0 + SLOTS * i + slot;
     const bool ok = row < r1;  // wave-uniform
     const int64_t base = row * p.d;
-    float a[BW_CHUNKS][8], b[BW_CHUNKS][8];
+    float a[U][8], b[U][8];
     float dot = 0.0f;  // this wave's share of sum_k dn*g*x
     const float r = ok ? p.rstd[row] : 0.0f;
 #pragma unroll
-    for (int u = 0; u < BW_CHUNKS; ++u) {
-      const int c = 8 * rl + 2048 * u;
+    for (int u = 0; u < U; ++u) {
+      const int c = 8 * rl + SPAN * u;
       if (ok && c < p.d) {
         float gv[8];
         ld8<DNDT>(p.dn, base + c, p.dn_dt, a[u]);
@@ -175,17 +182,20 @@ __global__ __launch_bounds__(BW_THREADS) void rmsnorm_bwd_rows_kernel(NormP p) {
         for (int e = 0; e < 8; ++e) dot += a[u][e] * gv[e] * b[u][e];
       }
     }
-    dot = wave_sum(dot);
-    if (lane == 0) dots[i & 1][slot][wr] = dot;
-    __syncthreads();
+    float tot = wave_sum(dot);
+    if constexpr (WPR > 1) {
+      if (lane == 0) dots[i & 1][slot][wr] = tot;
+      __syncthreads();
+      tot = dots[i & 1][slot][0];
+#pragma unroll
+      for (int w = 1; w < WPR; ++w) tot += dots[i & 1][slot][w];
+    }
     if (!ok) continue;
-    const float tot = dots[i & 1][slot][0] + dots[i & 1][slot][1] + dots[i & 1][slot][2] +
-                      dots[i & 1][slot][3];
     const float mean = tot * r / (float)p.d;  // mean_k(dxh * xh)
     const float r2m = r * mean;
 #pragma unroll
-    for (int u = 0; u < BW_CHUNKS; ++u) {
-      const int c = 8 * rl + 2048 * u;
+    for (int u = 0; u < U; ++u) {
+      const int c = 8 * rl + SPAN * u;
       if (c < p.d) {
         float o[8], gv[8];
         ld8<WDT>(p.g, c, p.w_dt, gv);
@@ -206,24 +216,21 @@ __global__ __launch_bounds__(BW_THREADS) void rmsnorm_bwd_rows_kernel(NormP p) {
     }
   }
   if (!p.part) return;  // uniform: no gain gradient requested
-#pragma unroll 1
-  for (int s = 0; s < 4; ++s) {
-    if (slot == s) {
 #pragma unroll
-      for (int u = 0; u < BW_CHUNKS; ++u) {
-        const int c = 8 * rl + 2048 * u;
-        if (c < p.d) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) red[c + e] = (s == 0 ? 0.0f : red[c + e]) + acc[u][e];
-        }
-      }
-    }
-    __syncthreads();
+  for (int u = 0; u < U; ++u) {
+    const int c = 8 * rl + SPAN * u;
+    if (c < p.d) store8_dt(red[slot], c, LC_FP32, acc[u]);
   }
-  for (int k = threadIdx.x; k < p.d; k += BW_THREADS) p.partial[(int64_t)blockIdx.x * p.d + k] = red[k];
+  __syncthreads();
+  for (int k = threadIdx.x; k < p.d; k += BW_THREADS) {
+    float t = red[0][k];
+#pragma unroll
+    for (int w = 1; w < SLOTS; ++w) t += red[w][k];
+    p.partial[(int64_t)blockIdx.x * p.d + k] = t;
+  }
 }
 
-// Rows longer than MAXD: one workgroup of 4 waves per kNormRowsPerBlock rows
+// Rows longer than MAXB: one workgroup of 4 waves per kNormRowsPerBlock rows
 // (wave w: rows w, w + 4, ...), each row read twice; the gain gradient's
 // partial sums come from rmsnorm_dg_partial_kernel.
 __global__ __launch_bounds__(256) void rmsnorm_bwd_long_kernel(NormP p) {
@@ -239,7 +246,7 @@ __device__ __forceinline__ float ld1_dt(const void *base, int64_t i, int dt) {
   return (float)static_cast<const _Float16 *>(base)[i];
 }
 
-// rows longer than MAXD: partial[blk][k] = sum over rows of block blk of dn[t,k] * x[t,k] * rstd[t]
+// rows longer than MAXB: partial[blk][k] = sum over rows of block blk of dn[t,k] * x[t,k] * rstd[t]
 __global__ __launch_bounds__(256) void rmsnorm_dg_partial_kernel(NormP p) {
   const int k = blockIdx.x * 256 + threadIdx.x;
   if (k >= p.d) return;
@@ -335,10 +342,15 @@ lc_status rmsnorm_fwd_launch(const lc_norm_args &a, hipStream_t s) {
   LC_TRY(check_common(a, false));
   const NormP p = make_params(a);
   const dim3 grid((unsigned)((a.T + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK));
-  // the decoder stage's type mix (fp32 residual rows, bf16 gain and output)
-  // has its own instantiation; every other mix takes the generic kernel
+  // the stages' type mixes (bf16: gain and output bf16, rows fp32 or, in the first
+  // layer, bf16; fp32: all fp32) have their own instantiations; every other mix
+  // takes the generic kernel
   if (p.x_dt == LC_FP32 && p.w_dt == LC_BF16 && p.out_dt == LC_BF16)
     hipLaunchKernelGGL((rmsnorm_fwd_kernel<LC_FP32, LC_BF16, LC_BF16>), grid, dim3(256), 0, s, p);
+  else if (p.x_dt == LC_BF16 && p.w_dt == LC_BF16 && p.out_dt == LC_BF16)
+    hipLaunchKernelGGL((rmsnorm_fwd_kernel<LC_BF16, LC_BF16, LC_BF16>), grid, dim3(256), 0, s, p);
+  else if (p.x_dt == LC_FP32 && p.w_dt == LC_FP32 && p.out_dt == LC_FP32)
+    hipLaunchKernelGGL((rmsnorm_fwd_kernel<LC_FP32, LC_FP32, LC_FP32>), grid, dim3(256), 0, s, p);
   else
     hipLaunchKernelGGL((rmsnorm_fwd_kernel<-1, -1, -1>), grid, dim3(256), 0, s, p);
   return check_launch("rmsnorm_fwd_kernel");
@@ -346,19 +358,43 @@ lc_status rmsnorm_fwd_launch(const lc_norm_args &a, hipStream_t s) {
 
 namespace {
 
-// Row kernel, plus the separate partial-sum kernel for rows longer than MAXD
+template <int DNDT, int XDT, int WDT, int RDT, int ODT>
+void bwd_rows_typed(const NormP &p, hipStream_t s) {
+  const dim3 grid((unsigned)p.nblk), block(BW_THREADS);
+  if (p.d <= 512)
+    hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<1, 1, DNDT, XDT, WDT, RDT, ODT>), grid, block, 0, s, p);
+  else if (p.d <= 1024)
+    hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<2, 1, DNDT, XDT, WDT, RDT, ODT>), grid, block, 0, s, p);
+  else if (p.d <= 2048)
+    hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<4, 1, DNDT, XDT, WDT, RDT, ODT>), grid, block, 0, s, p);
+  else if (p.d <= 4096)
+    hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<4, 2, DNDT, XDT, WDT, RDT, ODT>), grid, block, 0, s, p);
+  else
+    hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<8, 2, DNDT, XDT, WDT, RDT, ODT>), grid, block, 0, s, p);
+}
+
+// Row kernel, plus the separate partial-sum kernel for rows longer than MAXB
 // when p.part is set.
 lc_status bwd_rows(const NormP &p, hipStream_t s) {
-  if (p.d <= MAXD) {
-    // the decoder stage's type mix (fp32 dn, x, residual gradient and dx, bf16
-    // gain) has its own instantiation; every other mix takes the generic kernel
-    if (p.dn_dt == LC_FP32 && p.x_dt == LC_FP32 && p.w_dt == LC_BF16 && p.out_dt == LC_FP32 &&
-        (!p.dres || p.dres_dt == LC_FP32))
-      hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<LC_FP32, LC_FP32, LC_BF16, LC_FP32, LC_FP32>),
-                         dim3((unsigned)p.nblk), dim3(BW_THREADS), 0, s, p);
+  if (p.d <= MAXB) {
+    // The stages' type mixes have their own instantiations (straight-line loads);
+    // every other mix takes the generic kernel. A bf16 stage: fp32 dn, bf16 gain;
+    // x and dx bf16 in the first layer, the residual gradient bf16 in the last, the
+    // rest fp32. An fp32 stage: all fp32.
+    const bool f32x = p.x_dt == LC_FP32, f32o = p.out_dt == LC_FP32;
+    const bool f32r = !p.dres || p.dres_dt == LC_FP32;
+    const bool stage = p.dn_dt == LC_FP32 && p.w_dt == LC_BF16 && (f32x || p.x_dt == LC_BF16) &&
+                       (f32o || p.out_dt == LC_BF16) && (f32r || p.dres_dt == LC_BF16);
+    if (stage && f32x && f32o && f32r)
+      bwd_rows_typed<LC_FP32, LC_FP32, LC_BF16, LC_FP32, LC_FP32>(p, s);
+    else if (stage && f32x && f32o)
+      bwd_rows_typed<LC_FP32, LC_FP32, LC_BF16, LC_BF16, LC_FP32>(p, s);
+    else if (stage && !f32x && !f32o && f32r)
+      bwd_rows_typed<LC_FP32, LC_BF16, LC_BF16, LC_FP32, LC_BF16>(p, s);
+    else if (p.dn_dt == LC_FP32 && p.w_dt == LC_FP32 && f32x && f32o && f32r)
+      bwd_rows_typed<LC_FP32, LC_FP32, LC_FP32, LC_FP32, LC_FP32>(p, s);
     else
-      hipLaunchKernelGGL((rmsnorm_bwd_rows_kernel<-1, -1, -1, -1, -1>), dim3((unsigned)p.nblk),
-                         dim3(BW_THREADS), 0, s, p);
+      bwd_rows_typed<-1, -1, -1, -1, -1>(p, s);
     return check_launch("rmsnorm_bwd_rows_kernel");
   }
   hipLaunchKernelGGL(rmsnorm_bwd_long_kernel, dim3((unsigned)p.nblk), dim3(256), 0, s, p);
