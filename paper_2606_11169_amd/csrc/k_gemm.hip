@@ -149,10 +149,6 @@ struct Stream {
     const uint32_t off = ok ? base + step(t) * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
     dma16(rs, lds + (8 * wave + t) * RUN, off);
   }
-  __device__ __forceinline__ void load(i32x4_v rs, lds_t *lds, int wave, int k0, int K) const {
-#pragma unroll
-    for (int t = 0; t < 8; ++t) load1(rs, lds, wave, k0, K, t);
-  }
 };
 
 // MFMA operand of 16 rows (row0 .. row0+15) at k = 32 s + 8 (lane / 16) + [0, 8)
@@ -216,21 +212,32 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
   const uint32_t kbw = gk ? 2u : (uint32_t)((grp == 0 ? p.lda : p.ldb) * 2);
   lds_t *const dst0 = R0 + grp * OPND_BYTES + 8 * w4 * RUN;
   const bool ragged = (kend - kbeg) % KS != 0;
-  auto load = [&](int st) {  // this group's operand of stage st
+  auto load = [&](int st, int t0, int t1) {  // runs t0 .. t1 - 1 of this group's operand of stage st
+    if (st >= ns) return;
     if (ragged && st == ns - 1) {
       lds_t *stage = R0 + (st & 1) * STAGE_BYTES;
-      if (grp == 0) sa_.load(rs, stage, w4, kbeg + st * KS, kend);
-      else sb_.load(rs, stage + OPND_BYTES, w4, kbeg + st * KS, kend);
+#pragma unroll
+      for (int t = t0; t < t1; ++t) {
+        if (grp == 0) sa_.load1(rs, stage, w4, kbeg + st * KS, kend, t);
+        else sb_.load1(rs, stage + OPND_BYTES, w4, kbeg + st * KS, kend, t);
+      }
       return;
     }
     lds_t *d = dst0 + (st & 1) * STAGE_BYTES;
     const uint32_t so = (uint32_t)(st * KS) * kbw;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) dma16s(rs, d + t * RUN, vo[t], so);
+    for (int t = t0; t < t1; ++t) dma16s(rs, d + t * RUN, vo[t], so);
   };
 
   // A stage is multiplied in four steps of 16 MFMAs: k half q (32 k), row half h
-  // of the wave's 64 rows.
+  // of the wave's 64 rows. The barrier that publishes stage st + 1 (each wave's
+  // loads of it and fragment reads of stage st done) sits before stage st's last
+  // step, and frees stage st's buffer: half of stage st + 2's loads are issued
+  // right there, the other half a step later. All eight at the start of stage st
+  // + 1 leave a step less to arrive in and a fuller load queue (7B-shaped layer
+  // forward + backward 5245 us against 5120 this way); all eight right after the
+  // barrier collide with the fragment reads (2% slower products), and later
+  // loads, in twos over the steps, arrive late (3%).
   bf16x8_v fa[FM], fb[2][FN];
   auto read_a = [&](int st, int q, int h) {
     const lds_t *t = R0 + (st & 1) * STAGE_BYTES;
@@ -250,15 +257,16 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[q][j], fa[i], acc[i][j], 0, 0, 0);
   };
   constexpr int RDA = A_K ? 2 : 4, RDB = B_K ? FN : 2 * FN;  // LDS reads of half A's, of B's fragments
-  if (ns > 0) load(0);
+  load(0, 0, 8);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   __syncthreads();
   if (ns > 0) {
     read_a(0, 0, 0);
     read_b(0, 0);
+    load(1, 0, 4);
   }
   for (int st = 0; st < ns; ++st) {
-    if (st + 1 < ns) load(st + 1);
+    load(st + 1, 4, 8);
     read_a(st, 0, 1);
     multiply(0, 0);
     interleave_steps<RDA, 16>();
@@ -274,6 +282,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
     __syncthreads();
+    load(st + 2, 0, 4);
     // (after the last stage this reads the other buffer's stale data, unused)
     read_a(st + 1, 0, 0);
     read_b(st + 1, 0);
