@@ -334,21 +334,32 @@ __global__ __launch_bounds__(256) void moe_router_partial_kernel(RouterGradP p) 
   }
   __syncthreads();
   if (i >= p.d) return;
-#pragma unroll 4
-  for (int64_t t = t0; t < t1; ++t) {
-    const int tl = (int)(t - t0);
+  // a block's sum is a chain of loads of one column: sixteen in flight
+  const int nt = (int)(t1 - t0);
+  auto load = [&](int tl) -> float {
+    const int64_t o = (t0 + tl) * p.d + i;
+    if constexpr (ND == LC_FP32) return static_cast<const float *>(p.n)[o];
+    else if constexpr (ND == LC_BF16) return (float)static_cast<const __bf16 *>(p.n)[o];
+    else return (float)static_cast<const _Float16 *>(p.n)[o];
+  };
+  auto add = [&](int tl, float x) {
     const int e0 = ssel[2 * tl] - eg, e1 = ssel[2 * tl + 1] - eg;  // (the pair's experts differ)
     const float d0 = sdl[2 * tl], d1 = sdl[2 * tl + 1];
-    float x;
-    if constexpr (ND == LC_FP32) x = static_cast<const float *>(p.n)[t * p.d + i];
-    else if constexpr (ND == LC_BF16) x = (float)static_cast<const __bf16 *>(p.n)[t * p.d + i];
-    else x = (float)static_cast<const _Float16 *>(p.n)[t * p.d + i];
 #pragma unroll
     for (int k = 0; k < kRouterExpertsPerPass; ++k) {
       const float c = k == e0 ? d0 : (k == e1 ? d1 : 0.0f);
       s[k] += c * x;
     }
+  };
+  int tl = 0;
+  for (; tl + 16 <= nt; tl += 16) {
+    float x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = load(tl + u);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) add(tl + u, x[u]);
   }
+  for (; tl < nt; ++tl) add(tl, load(tl));
 #pragma unroll
   for (int k = 0; k < kRouterExpertsPerPass; ++k)
     if (eg + k < p.E) p.partial[((int64_t)blk * p.E + eg + k) * p.d + i] = s[k];
@@ -358,7 +369,16 @@ __global__ __launch_bounds__(256) void moe_router_final_kernel(RouterGradP p) {
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;  // e * d + i
   if (j >= (int64_t)p.E * p.d) return;
   float s = 0.0f;
-  for (int b = 0; b < p.nblk; ++b) s += p.partial[(int64_t)b * p.E * p.d + j];
+  const int64_t ed = (int64_t)p.E * p.d;
+  int b = 0;
+  for (; b + 16 <= p.nblk; b += 16) {  // (sixteen loads in flight, added in order)
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = p.partial[(b + i) * ed + j];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s += v[i];
+  }
+  for (; b < p.nblk; ++b) s += p.partial[b * ed + j];
   p.g[j] = p.g[j] + s;
 }
 
