@@ -79,6 +79,13 @@ __device__ __forceinline__ void dma16s(i32x4_v rs, lds_t *lds, uint32_t voff, ui
                : "memory", "m0");
 }
 
+// at most LEFT of this wave's loads in flight and its LDS reads done, then the
+// workgroup's barrier
+template <int LEFT>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LEFT) : "memory");
+}
+
 // Scheduling pattern for one k-step: the NRD LDS reads of the next k-step
 // spread over the NMF MFMAs of this one (reads first, as evenly as possible).
 template <int NRD, int NMF, int I = 0>

@@ -5,16 +5,21 @@
 // These products are small (a tiny stage's outputs are 128 x 128 to 128 x 688),
 // so one workgroup's serial chain and the number of launches bound them. Every
 // workgroup of four waves owns a 32 x 32 or 64 x 64 output tile and the waves
-// split k: wave w multiplies the 32-deep steps w, w + 4, ... of the whole tile,
-// so no operand value is read by two waves and nothing is staged: fragments go
-// from global memory straight into registers, the next step's while one
-// multiplies. The four partial tiles are added in wave order through LDS, where
-// RoPE and SwiGLU find the two columns they combine (the tile's columns are
-// chosen as such pairs), so each product is one launch. (With 64 x 64 tiles
+// split k, so no operand value is read by two waves. The four partial tiles are
+// added in wave order through LDS, where RoPE and SwiGLU find the two columns they
+// combine (the tile's columns are chosen as such pairs), so each product is one
+// launch. (With 64 x 64 tiles
 // staged through LDS by scalar loads, and RoPE and SwiGLU as launches of their
 // own, a 128 x 384 x 128 product took 38 us and a 400-token d-768 layer's 195 us
 // on average.)
-#include "common.hpp"
+//
+// Operands come in through a ring of four LDS stages (LDS-DMA loads of whole cache
+// lines, three stages ahead, one barrier per stage) where rows are whole 16-byte
+// runs; else fragments go from global memory straight into registers, a step
+// ahead. (Rows read 32 bytes at a time in fragment order fill the L1 several times
+// over: the register form took 923 us for two microbatches' products of a 400-token
+// d-768 layer, forward and backward, the ring 700.)
+#include "gemm_common.hpp"
 
 namespace lc {
 namespace {
@@ -35,6 +40,7 @@ struct F32P {
   int epi;
   int rope_cols, rope_seq, hd;
   int vec_a, vec_b;  // k-major rows of whole 16-byte runs
+  uint32_t a_bytes, b_bytes;  // byte extents (ring kernel)
   unsigned tiles_n;
 };
 
@@ -60,6 +66,226 @@ __device__ __forceinline__ int column(const F32P &p, int tn, int j, int *n, bool
   return *n;
 }
 
+// The waves' partial tiles added in wave order and the epilogue. `part`: NW
+// tiles of T rows of T + 1 floats of LDS that no wave reads any more.
+template <int T>
+__device__ __forceinline__ void finish(const F32P &p, float *part, const f32x16_v (&acc)[T / 32][T / 32], int m0,
+                                       int tn, int w, int lane) {
+  constexpr int F = T / 32, LD = T + 1;
+  const int l32 = lane & 31, h = lane >> 5;
+  // lane: column l32 of a block, rows (r & 3) + 8 (r >> 2) + 4 h
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        part[w * T * LD + (32 * i + (r & 3) + 8 * (r >> 2) + 4 * h) * LD + 32 * j + l32] = acc[i][j][r];
+  __syncthreads();
+  auto sum = [&](int r, int c) {
+    float v = part[r * LD + c];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) v += part[i * T * LD + r * LD + c];
+    return v;
+  };
+  const bool pair = p.epi == LC_EPI_SWIGLU || p.epi == LC_EPI_ROPE;
+  const int cols = pair ? T / 2 : T;
+  const int tid = threadIdx.x, j = tid % cols;
+  int n;
+  bool ok;
+  column<T>(p, tn, j, &n, &ok);
+  if (!ok) return;
+  for (int r = tid / cols; r < T; r += 64 * NW / cols) {
+    const int m = m0 + r;
+    if (m >= p.M) break;
+    const float v = sum(r, j);
+    float *c = p.C + (int64_t)m * p.ldc + n;
+    switch (p.epi) {
+      case LC_EPI_ACCUM_F32: *c = *c + v; break;
+      case LC_EPI_RESIDUAL: *c = p.R[(int64_t)m * p.ldr + n] + v; break;
+      case LC_EPI_SWIGLU_BWD: {
+        const float g = p.aux0[(int64_t)m * p.ld_aux + n];
+        const float u = p.aux1[(int64_t)m * p.ld_aux + n];
+        const float s = sigmoidf_(g);
+        c[0] = v * u * s * (1.0f + g * (1.0f - s));
+        c[p.N] = v * g * s;
+        break;
+      }
+      case LC_EPI_SWIGLU: {
+        const float u = sum(r, j + T / 2);
+        p.aux0[(int64_t)m * p.ld_aux + n] = v;
+        p.aux1[(int64_t)m * p.ld_aux + n] = u;
+        *c = v * sigmoidf_(v) * u;
+        break;
+      }
+      case LC_EPI_ROPE: {
+        const float y = sum(r, j + T / 2);
+        const int half = p.hd / 2;
+        if (n < p.rope_cols) {
+          const int64_t t = (int64_t)(m % p.rope_seq) * half + n % p.hd;
+          const float cs = p.rcos[t], sn = p.rsin[t];
+          c[0] = v * cs - y * sn;
+          c[half] = v * sn + y * cs;
+        } else {
+          c[0] = v;
+          c[half] = y;
+        }
+        break;
+      }
+      default: *c = v; break;
+    }
+  }
+}
+
+// ------------------------------------------------------------------ ring
+// A slice of 32 k of an operand (T rows) in LDS, 32 T floats: T / 8 runs of 1 KiB.
+//   k-major: row r is position r / (T / 8) of run r % (T / 8) (128 bytes, eight
+//     chunks of four k), chunk c at c ^ swz(r): the 16 rows that one phase of a
+//     fragment read takes at one chunk then touch all 64 banks
+//   m/n-major: k rows of T floats, one after the other
+template <int T, bool KMAJ>
+struct Slice {
+  static constexpr int RUNS = T / 8, BYTES = RUNS * 1024;
+  __device__ __forceinline__ static int swz(int r) { return T == 64 ? r & 7 : (r & 3) + 4 * ((r >> 3) & 1); }
+  // this lane's part of run q: first k of the slice, tile row (m/n-major: first of 4)
+  __device__ __forceinline__ static void part(int q, int lane, int *k, int *row) {
+    if constexpr (KMAJ) {
+      *row = (lane >> 3) * RUNS + q;
+      *k = 4 * ((lane & 7) ^ swz(*row));
+    } else {
+      const int f = 256 * q + 4 * lane;  // float of the slice
+      *k = f / T;
+      *row = f % T;
+    }
+  }
+  // x[u] = row 32 f + lane % 32 at k = k0 + 4 (lane / 32) + u, k0 a multiple of 8
+  __device__ __forceinline__ static void frag(const lds_t *t, int f, int k0, int lane, float (&x)[4]) {
+    const int r = 32 * f + (lane & 31), k = k0 + 4 * (lane >> 5);
+    if constexpr (KMAJ) {
+      typedef __attribute__((address_space(3))) f32x4_v lds_f4;
+      const f32x4_v v = *reinterpret_cast<const lds_f4 *>(t + (r % RUNS) * 1024 + (r / RUNS) * 128 +
+                                                          (((k >> 2) ^ swz(r)) << 4));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = v[u];
+    } else {
+      typedef __attribute__((address_space(3))) float lds_f;
+      const lds_f *s = reinterpret_cast<const lds_f *>(t) + k * T + r;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = s[u * T];
+    }
+  }
+};
+
+constexpr int NST = 4;  // stages of the ring
+
+// SUB slices per stage; every wave multiplies 32 SUB / 4 k of each stage
+template <int T, bool A_K, bool B_K>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_ring_kernel(F32P p) {
+  constexpr int F = T / 32, SUB = 64 / T, KS = 32 * SUB, G = SUB;  // G: groups of 8 k per wave and stage
+  constexpr int OPB = Slice<T, true>::BYTES, STAGE = 2 * SUB * OPB;
+  constexpr int LPW = 2 * SUB * (T / 8) / NW;  // loads per wave and stage: A by waves 0, 1, B by 2, 3
+  constexpr int PART = NW * T * (T + 1) * 4;
+  static_assert(KS == NW * 8 * G && LPW == 4, "");
+  __shared__ __align__(16) char ring[NST * STAGE > PART ? NST * STAGE : PART];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = (int)(blockIdx.x / p.tiles_n) * T, tn = (int)(blockIdx.x % p.tiles_n);
+  const int grp = w >> 1, wo = w & 1;
+  const i32x4_v rs = grp == 0 ? make_rsrc(p.A, p.a_bytes) : make_rsrc(p.B, p.b_bytes);
+  const bool gk = grp == 0 ? A_K : B_K;
+  const int64_t ld = grp == 0 ? p.lda : p.ldb;
+  const int sub = wo * LPW / (T / 8), q0 = wo * LPW % (T / 8);
+  uint32_t vo[LPW];  // byte offsets of this wave's runs in stage 0
+  int kl[LPW];       // their k in the stage
+#pragma unroll
+  for (int t = 0; t < LPW; ++t) {
+    int k, r, row;
+    bool ok = true;
+    if (gk) Slice<T, true>::part(q0 + t, lane, &k, &r);
+    else Slice<T, false>::part(q0 + t, lane, &k, &r);
+    if (grp == 0) {
+      row = m0 + r;
+      ok = row < p.M;
+    } else {
+      int n;
+      row = column<T>(p, tn, r, &n, &ok);
+    }
+    kl[t] = k + 32 * sub;
+    vo[t] = ok ? (uint32_t)((gk ? (int64_t)row * ld + kl[t] : (int64_t)kl[t] * ld + row) * 4) : OOB;
+  }
+  const uint32_t kbw = gk ? 4u : (uint32_t)(ld * 4);
+  lds_t *const R0 = LDS_AS(char, ring);
+  lds_t *const dst0 = R0 + (2 * sub + grp) * OPB + q0 * 1024;
+  const int ns = (p.K + KS - 1) / KS;
+  auto load = [&](int st) {
+    lds_t *d = dst0 + (st & (NST - 1)) * STAGE;
+    const uint32_t so = (uint32_t)(st * KS) * kbw;
+    if ((st + 1) * KS > p.K) {  // the stage ends past K: every lane checked
+#pragma unroll
+      for (int t = 0; t < LPW; ++t)
+        dma16(rs, d + t * 1024, st * KS + kl[t] < p.K && vo[t] != OOB ? vo[t] + so : OOB);
+      return;
+    }
+#pragma unroll
+    for (int t = 0; t < LPW; ++t) dma16s(rs, d + t * 1024, vo[t], so);
+  };
+  f32x16_v acc[F][F];
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  // wave w's k of a stage: 8 G w .. + 8 G - 1
+  const int ws = 8 * G * w / 32, wk = 8 * G * w % 32;
+  auto read = [&](int st, float (&a)[F][G][4], float (&b)[F][G][4]) {
+    const lds_t *t = R0 + (st & (NST - 1)) * STAGE + 2 * ws * OPB;
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        Slice<T, A_K>::frag(t, f, wk + 8 * g, lane, a[f][g]);
+        Slice<T, B_K>::frag(t + OPB, f, wk + 8 * g, lane, b[f][g]);
+      }
+  };
+  auto multiply = [&](const float (&a)[F][G][4], const float (&b)[F][G][4]) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+          for (int j = 0; j < F; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][g][u], b[j][g][u], acc[i][j], 0, 0, 0);
+  };
+  float fa[2][F][G][4], fb[2][F][G][4];
+  auto step = [&](int st, float (&a)[F][G][4], float (&b)[F][G][4], float (&an)[F][G][4], float (&bn)[F][G][4]) {
+    const int later = ns - 2 - st;  // stages after st + 1, in flight at most two
+    if (later >= 2) wait_barrier<2 * LPW>();
+    else if (later == 1) wait_barrier<LPW>();
+    else wait_barrier<0>();
+    if (st + NST < ns) load(st + NST);
+    read(st + 1, an, bn);  // (after the last stage: another slot's stale data, unused)
+    multiply(a, b);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll 1
+  for (int st = 0; st < min(ns, NST); ++st) load(st);
+  if (ns >= 4) wait_barrier<3 * LPW>();
+  else if (ns == 3) wait_barrier<2 * LPW>();
+  else if (ns == 2) wait_barrier<LPW>();
+  else wait_barrier<0>();
+  read(0, fa[0], fb[0]);
+  for (int st = 0; st < ns; st += 2) {
+    step(st, fa[0], fb[0], fa[1], fb[1]);
+    if (st + 1 < ns) step(st + 1, fa[1], fb[1], fa[0], fb[0]);
+  }
+  __syncthreads();  // every wave's last fragment reads are done
+  finish<T>(p, reinterpret_cast<float *>(ring), acc, m0, tn, w, lane);
+}
+
+// ------------------------------------------------------------------ registers
 // One lane's operand values of a 32-deep step at k: x[4 jj + c] is k + 8 jj + 4 h
 // + c (h = lane / 32) of operand row `row` (k-major) or column `row`; values at or
 // past K are 0. Both operands use this order, so any layouts can meet.
@@ -99,8 +325,7 @@ __device__ __forceinline__ void load_step(const float *X, int64_t ld, int row, i
 template <int T, bool A_K, bool B_K>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(F32P p) {
   constexpr int F = T / 32;        // 32 x 32 blocks per side
-  constexpr int LD = T + 1;        // row stride of a partial tile in LDS
-  __shared__ float part[NW][T * LD];
+  __shared__ float part[NW * T * (T + 1)];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
@@ -148,77 +373,23 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(F32P p) {
     if (k + 2 * STEP < p.K) load(k + 2 * STEP, a[0], b[0]);
     multiply(a[1], b[1]);
   }
-  // lane: column l32 of a block, rows (r & 3) + 8 (r >> 2) + 4 h
-#pragma unroll
-  for (int i = 0; i < F; ++i)
-#pragma unroll
-    for (int j = 0; j < F; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        part[w][(32 * i + (r & 3) + 8 * (r >> 2) + 4 * h) * LD + 32 * j + l32] = acc[i][j][r];
-  __syncthreads();
-  auto sum = [&](int r, int c) {
-    float v = part[0][r * LD + c];
-#pragma unroll
-    for (int i = 1; i < NW; ++i) v += part[i][r * LD + c];
-    return v;
-  };
-  const bool pair = p.epi == LC_EPI_SWIGLU || p.epi == LC_EPI_ROPE;
-  const int cols = pair ? T / 2 : T;
-  const int j = tid % cols;
-  int n;
-  bool ok;
-  column<T>(p, tn, j, &n, &ok);
-  if (!ok) return;
-  for (int r = tid / cols; r < T; r += 64 * NW / cols) {
-    const int m = m0 + r;
-    if (m >= p.M) break;
-    const float v = sum(r, j);
-    float *c = p.C + (int64_t)m * p.ldc + n;
-    switch (p.epi) {
-      case LC_EPI_ACCUM_F32: *c = *c + v; break;
-      case LC_EPI_RESIDUAL: *c = p.R[(int64_t)m * p.ldr + n] + v; break;
-      case LC_EPI_SWIGLU_BWD: {
-        const float g = p.aux0[(int64_t)m * p.ld_aux + n];
-        const float u = p.aux1[(int64_t)m * p.ld_aux + n];
-        const float s = sigmoidf_(g);
-        c[0] = v * u * s * (1.0f + g * (1.0f - s));
-        c[p.N] = v * g * s;
-        break;
-      }
-      case LC_EPI_SWIGLU: {
-        const float u = sum(r, j + T / 2);
-        p.aux0[(int64_t)m * p.ld_aux + n] = v;
-        p.aux1[(int64_t)m * p.ld_aux + n] = u;
-        *c = v * sigmoidf_(v) * u;
-        break;
-      }
-      case LC_EPI_ROPE: {
-        const float y = sum(r, j + T / 2);
-        const int half = p.hd / 2;
-        if (n < p.rope_cols) {
-          const int64_t t = (int64_t)(m % p.rope_seq) * half + n % p.hd;
-          const float cs = p.rcos[t], sn = p.rsin[t];
-          c[0] = v * cs - y * sn;
-          c[half] = v * sn + y * cs;
-        } else {
-          c[0] = v;
-          c[half] = y;
-        }
-        break;
-      }
-      default: *c = v; break;
-    }
-  }
+  finish<T>(p, part, acc, m0, tn, w, lane);
 }
 
 template <int T>
-lc_status run_f32(F32P p, bool ak, bool bk, hipStream_t s) {
+lc_status run_f32(F32P p, bool ak, bool bk, bool ring, hipStream_t s) {
   const int cols = p.epi == LC_EPI_SWIGLU ? T / 2 : T;
   const int64_t tm = ((int64_t)p.M + T - 1) / T, tn = ((int64_t)p.N + cols - 1) / cols;
   if (tm * tn > INT32_MAX / (64 * NW)) return fail(LC_ERR_UNSUPPORTED, "gemm fp32: output too large");
   p.tiles_n = (unsigned)tn;
   const dim3 grid((unsigned)(tm * tn)), block(64 * NW);
+  if (ring) {
+    if (ak && bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, true, true>), grid, block, 0, s, p);
+    else if (ak) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, true, false>), grid, block, 0, s, p);
+    else if (bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((gemm_f32_ring_kernel<T, false, false>), grid, block, 0, s, p);
+    return check_launch("gemm_f32_ring_kernel");
+  }
   if (ak && bk) hipLaunchKernelGGL((gemm_f32_kernel<T, true, true>), grid, block, 0, s, p);
   else if (ak) hipLaunchKernelGGL((gemm_f32_kernel<T, true, false>), grid, block, 0, s, p);
   else if (bk) hipLaunchKernelGGL((gemm_f32_kernel<T, false, true>), grid, block, 0, s, p);
@@ -259,7 +430,17 @@ lc_status gemm_f32_launch(const lc_gemm_args &a, hipStream_t s) {
   const int64_t n = a.epilogue == LC_EPI_SWIGLU ? 2 * a.N : a.N;
   const int64_t tiles64 = ((a.M + 63) / 64) * ((n + 63) / 64);
   const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
-  return tiles64 >= 192 ? run_f32<64>(p, ak, bk, s) : run_f32<32>(p, ak, bk, s);
+  // The ring's loads are 16 bytes: rows of whole 16-byte runs of which none is part
+  // inside the operand (a part past K would not be zero), 32-bit offsets
+  const int64_t brows = a.epilogue == LC_EPI_SWIGLU ? 2 * a.N : a.N;
+  const int64_t ae = 4 * (ak ? (a.M - 1) * a.lda + a.K : (a.K - 1) * a.lda + a.M);
+  const int64_t be = 4 * (bk ? (brows - 1) * a.ldb + a.K : (a.K - 1) * a.ldb + brows);
+  const bool ring = p.vec_a && p.vec_b && (!(ak || bk) || a.K % 4 == 0) && (ak || a.M % 4 == 0) &&
+                    (bk || (a.N % 4 == 0 && a.epilogue != LC_EPI_ROPE)) &&
+                    ae < (int64_t)OOB && be < (int64_t)OOB;
+  p.a_bytes = (uint32_t)ae;
+  p.b_bytes = (uint32_t)be;
+  return tiles64 >= 192 ? run_f32<64>(p, ak, bk, ring, s) : run_f32<32>(p, ak, bk, ring, s);
 }
 
 }  // namespace lc

@@ -104,13 +104,6 @@ struct Opnd {
   }
 };
 
-// at most LEFT of this wave's loads in flight and its LDS reads done, then the
-// workgroup's barrier
-template <int LEFT>
-__device__ __forceinline__ void wait_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(LEFT) : "memory");
-}
-
 template <int T, bool A_K, bool B_K, int EPI, int TM>
 __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
   using C = Cfg<T>;

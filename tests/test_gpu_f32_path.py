@@ -28,7 +28,8 @@ def close(got, ref, tol):
 
 
 @pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (33, 31, 5, 0), (130, 66, 129, 3), (128, 344, 128, 0),
-                                       (900, 970, 70, 0), (1030, 1024, 164, 4)])
+                                       (900, 970, 70, 0), (1030, 1024, 164, 4),
+                                       (36, 40, 8, 0), (400, 768, 516, 0), (1000, 1024, 264, 4)])
 @pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 1), (0, 0)])
 def test_products(M, N, K, pad, layout):
     ak, bk = layout
