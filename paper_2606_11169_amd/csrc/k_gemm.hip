@@ -546,12 +546,13 @@ static lc_status check_gemm_args(const lc_gemm_args &a) {
 // time per unit of k. One workgroup runs per compute unit with every tile size,
 // so a grid of t tiles takes ceil(t / 256) rounds. Measured ns per k and round
 // (2048 x 2048 to 4096 x 11008 outputs, all compute units busy): 26 with 256 x
-// 256 tiles, 8.5 with 128 x 128, 4.4 with 64 x 64; a 256 x 256 round that fills
-// only part of the chip takes 17.7 + 8.3 x the part. The larger tile does more
+// 256 tiles, 8.5 with 128 x 128, 4.4 with 64 x 64, about 2.2 with 32 x 32 (1.3 on a
+// half-full chip); a 256 x 256 round that fills// only part of the chip takes 17.7 + 8.3 x the part. The larger tile does more
 // work per round, the smaller ones fill the chip: 2048 x 2048 outputs (64, 256
 // or 1024 tiles) at K = 5632 take 107, 49 or 103 us; 2048 x 6144 at K = 2048
-// (192, 768 or 3072 tiles) 53, 60 or 135 us; 256 x 512 at K = 1408 (2, 8 or 32
-// tiles) 31, 13 or 9 us. The choice depends on the output's size and the
+// (192, 768 or 3072 tiles) 53, 60 or 135 us; 256 x 512 at K = 1408 (2, 8, 32 or 128
+// tiles) 31, 13, 9 or 6 us; 256 x 1536 at K = 512 with 64 or 32 (96 or 384 tiles)
+// 6.5 or 6.8. The choice depends on the output's size and the
 // grouping only, so products of the same shape add in the same order whatever
 // their epilogue (an accumulated and a stored gradient are the same bits).
 static int pick_tile(const lc_gemm_args &a) {
@@ -568,6 +569,8 @@ static int pick_tile(const lc_gemm_args &a) {
   const int64_t c256 = t256 / CU * 260 + (part ? 177 + 83 * part / CU : 0);
   const int64_t c128 = (tiles(128) + CU - 1) / CU * 85;
   const int64_t c64 = (tiles(64) + CU - 1) / CU * 44;
+  const int64_t c32 = (tiles(32) + CU - 1) / CU * 22;
+  if (c32 < c64 && c32 < c128 && c32 < c256) return 32;
   if (c64 < c128 && c64 < c256) return 64;
   return c128 < c256 ? 128 : 256;
 }

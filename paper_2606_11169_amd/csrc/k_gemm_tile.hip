@@ -1,18 +1,20 @@
-// bf16 GEMM with 128 x 128 or 64 x 64 output tiles: the products whose grid of
+// bf16 GEMM with 128 x 128, 64 x 64 or 32 x 32 output tiles: the products whose grid of
 // 256 x 256 tiles (k_gemm.hip) would leave most of the 256 compute units idle.
 // Same operands, layouts, epilogues and per-element arithmetic.
 //
 // What bounds such a product is not the matrix cores but the serial chain of
 // one tile: with few tiles per compute unit there is no second workgroup to
 // cover a stage's load latency. So k is split inside the workgroup as well:
-// every wave owns a 64 x 64 block of the tile for its own k-step of each stage
-// (the 128 tile: 8 waves = 2 x 2 blocks x 2 k-steps of a 64-deep stage; the 64
-// tile: 4 waves = 4 k-steps of a 128-deep stage), which halves (quarters) the
-// chain, reads no operand row of the 64 tile twice from LDS, and keeps both
+// every wave owns a block of the tile for its own k-steps of each stage (the 128
+// tile: 8 waves = 2 x 2 blocks of 64 x 64 x 2 k-steps of a 64-deep stage; the 64 and
+// 32 tiles: 4 waves, the whole tile each, one k-step of a 128-deep or two of a
+// 256-deep stage), which halves (quarters) the
+// chain, reads no operand row of the smaller tiles twice from LDS, and keeps both
 // (one) waves of a SIMD busy; the waves' partial tiles are added in k-step order
 // in the epilogue, through LDS. (At 2048 x 2048 x 11264 the 128 tile runs at 1040
 // TFLOP/s with one tile per compute unit; 64 tiles of 256 x 256 at 473. The 64
-// tile takes 9 us for a 256 x 512 x 1408 product, the 256 tile 31.) Operands stream HBM->LDS through a ring of four
+// tile takes 9 us for a 256 x 512 x 1408 product, the 256 tile 31; the 32 tile, with
+// four times the compute units loading, 6.) Operands stream HBM->LDS through a ring of four
 // stages, three stages ahead of the one being multiplied (the 256 tile's two 64
 // KiB stages leave no room for that; here a stage is 32 KiB), one barrier per
 // stage, the next stage's fragments read while one multiplies.
@@ -30,10 +32,14 @@ template <> struct Cfg<128> {
 template <> struct Cfg<64> {
   static constexpr int SUB = 2, WR = 1, KSPL = 4;
 };
+template <> struct Cfg<32> {
+  static constexpr int SUB = 4, WR = 1, KSPL = 4;
+};
+constexpr int threads(int tile) { return tile == 128 ? 512 : 256; }
 
-// What a tile column j of B is: B_PLAIN operand row n0 + j; B_ROPE (64 tile)
-// columns c0 + [0, 32) and 64 + c0 + [0, 32) of one head, so that a rotated
-// pair is in one tile; B_SWIGLU the first half gate rows, the second up rows.
+// What a tile column j of B is: B_PLAIN operand row n0 + j; B_ROPE columns c0 + [0,
+// T / 2) and 64 + c0 + [0, T / 2) of one head (the 128 tile: the whole head), so that
+// a rotated pair is in one tile; B_SWIGLU the first half gate rows, the second up rows.
 enum { B_PLAIN, B_ROPE, B_SWIGLU };
 
 // A slice of 64 k of an operand (T rows) in LDS: T / 8 runs of 1 KiB, RUN bytes
@@ -43,10 +49,12 @@ enum { B_PLAIN, B_ROPE, B_SWIGLU };
 //   k-major (128-byte rows, eight to a run), row r = 16 f + i:
 //     T = 128: position f of run i
 //     T = 64: position (f & 1) + 2 (i / 8) + 4 (f / 2) of run i % 8
+//     T = 32: position i / 4 + 4 f of run i % 4
 //   m/n-major (k rows of 2 T bytes), k row k:
 //     T = 128: position k / 16 (of 4) of run swap23(k % 16) (swap23 exchanges
 //       bits 2 and 3)
 //     T = 64: position bit2(k) + 2 bit4(k) + 4 bit5(k) of run (k & 3) + 4 bit3(k)
+//     T = 32: position k / 4 (of 16) of run k % 4
 template <int T, bool KMAJ>
 struct Opnd {
   static constexpr int RUNS = T / 8;
@@ -57,14 +65,16 @@ struct Opnd {
       const int i = lane & 15;
       const lds_t *p = t + (lane >> 4) * 16 + s * 64;
       if constexpr (T == 128) p += i * RUN + f * 128;
-      else p += (i & 7) * RUN + ((f & 1) + 2 * (i >> 3) + 4 * (f >> 1)) * 128;
+      else if constexpr (T == 64) p += (i & 7) * RUN + ((f & 1) + 2 * (i >> 3) + 4 * (f >> 1)) * 128;
+      else p += (i & 3) * RUN + ((i >> 2) + 4 * f) * 128;
       return *reinterpret_cast<const lds_v8 *>(p);
     } else {
       const int i16 = lane & 15, g = lane >> 4;
-      const lds_t *p = t + ((i16 >> 2) + 4 * (g & 1)) * RUN + f * 32 + (i16 & 3) * 8;
-      if constexpr (T == 128) p += ((g >> 1) + 2 * s) * 256;
-      else p += (2 * (g >> 1) + 4 * s) * 128;
-      constexpr int HI = T == 128 ? 8 * RUN : 128;  // k + 4
+      const lds_t *p = t + f * 32 + (i16 & 3) * 8;
+      if constexpr (T == 128) p += ((i16 >> 2) + 4 * (g & 1)) * RUN + ((g >> 1) + 2 * s) * 256;
+      else if constexpr (T == 64) p += ((i16 >> 2) + 4 * (g & 1)) * RUN + (2 * (g >> 1) + 4 * s) * 128;
+      else p += (i16 >> 2) * RUN + (2 * g + 8 * s) * 64;
+      constexpr int HI = T == 128 ? 8 * RUN : T == 64 ? 128 : 64;  // k + 4
       const s16x4_v v[2] = {__builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p)),
                             __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4 *)(p + HI))};
       return __builtin_bit_cast(bf16x8_v, v);
@@ -75,17 +85,18 @@ struct Opnd {
   __device__ __forceinline__ static int run_k(int q, int lane) {
     if constexpr (KMAJ) return 8 * (lane & 7);
     else if constexpr (T == 128) return (q & 3) + 8 * ((q >> 2) & 1) + 4 * (q >> 3) + 16 * (lane >> 4);
-    else {
+    else if constexpr (T == 64) {
       const int pos = lane >> 3;
       return (q & 3) + 8 * (q >> 2) + 4 * (pos & 1) + 16 * ((pos >> 1) & 1) + 32 * (pos >> 2);
-    }
+    } else return q + 4 * (lane >> 2);
   }
   // ... and its tile row (m/n-major: the first of 8)
   __device__ __forceinline__ static int run_row(int q, int lane) {
     if constexpr (!KMAJ) return 8 * (lane & (T / 8 - 1));
     const int pos = lane >> 3;
     if constexpr (T == 128) return 16 * pos + q;
-    else return 16 * ((pos & 1) + 2 * (pos >> 2)) + 8 * ((pos >> 1) & 1) + q;
+    else if constexpr (T == 64) return 16 * ((pos & 1) + 2 * (pos >> 2)) + 8 * ((pos >> 1) & 1) + q;
+    else return 16 * (pos >> 2) + 4 * (pos & 3) + q;
   }
 
   // byte offset of that part at k = k0 of the slice's first k (OOB: not in the operand)
@@ -96,8 +107,8 @@ struct Opnd {
     if constexpr (MAP == B_SWIGLU) {  // base: first output column; lim: gate rows
       chk = base + (j & (T / 2 - 1));
       row = j < T / 2 ? chk : lim + chk;
-    } else if constexpr (MAP == B_ROPE && T == 64) {  // base: 64 x tile column
-      row = chk = (base & ~127) + (base & 64) / 2 + (j & 31) + 2 * (j & 32);
+    } else if constexpr (MAP == B_ROPE && T < 128) {  // base: T x tile column
+      row = chk = (base & ~127) + (base & (128 - T)) / 2 + (j & (T / 2 - 1)) + (j < T / 2 ? 0 : 64);
     }
     if (chk >= lim) return OOB;
     return KMAJ ? (uint32_t)(((int64_t)row * ld + k) * 2) : (uint32_t)(((int64_t)k * ld + row) * 2);
@@ -105,9 +116,11 @@ struct Opnd {
 };
 
 template <int T, bool A_K, bool B_K, int EPI, int TM>
-__global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
+__global__ __launch_bounds__(threads(T)) void gemm_tile_kernel(GemmP p) {
   using C = Cfg<T>;
-  constexpr int NT = T * 4, NW = NT / 64, KS = 64 * C::SUB;
+  constexpr int NT = threads(T), NW = NT / 64, KS = 64 * C::SUB;
+  constexpr int FR = T / 16 / C::WR;           // 16-row fragments per side of a wave's block
+  constexpr int QS = KS / 32 / C::KSPL;        // k-steps per wave and stage
   constexpr int OPB = (T / 8) * RUN;           // one operand's 64-deep slice
   constexpr int STAGE = 2 * C::SUB * OPB;      // slices of A | B
   constexpr int LPW = C::SUB * (T / 8) / (NW / 2);  // loads per wave and stage
@@ -116,7 +129,7 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = wave / (C::WR * C::WR);  // this wave's k-step of a stage
+  const int kg = wave / (C::WR * C::WR);  // this wave's k-steps of a stage: QS kg ..
   const int wr = wave % (C::WR * C::WR) / C::WR, wc = wave % C::WR;
   constexpr bool SWI = EPI == LC_EPI_SWIGLU;
   constexpr int MAPB = SWI ? B_SWIGLU : EPI == LC_EPI_ROPE ? B_ROPE : B_PLAIN;
@@ -125,11 +138,11 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
   const int m0 = tile.m0, m_lim = tile.m_lim, kbeg = tile.kbeg, kend = tile.kend;
   const int n0 = SWI ? tile.tn * (T / 2) : tile.tn * T;
 
-  f32x4_v acc[4][4];
+  f32x4_v acc[FR][FR];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < FR; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_v{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int j = 0; j < FR; ++j) acc[i][j] = f32x4_v{0.0f, 0.0f, 0.0f, 0.0f};
 
   // the first half of the waves streams A, the second B: runs LPW wo .. + LPW - 1
   // of the operand's SUB T / 8 runs of a stage
@@ -138,51 +151,64 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
   const int grp = wave / (NW / 2), wo = wave % (NW / 2);
   const i32x4_v rs = grp == 0 ? make_rsrc(p.A, p.a_bytes) : make_rsrc(tile.B, p.b_bytes);
   uint32_t vo[LPW];
+  // run t of the wave: run qt(t) of slice st0 + sl(t)
   const int sub = wo * LPW / (T / 8), q0 = wo * LPW % (T / 8);
+  constexpr int RUNS = T / 8;
+  auto sl = [&](int t) { return LPW > RUNS ? t / RUNS : 0; };
+  auto qt = [&](int t) { return LPW > RUNS ? t % RUNS : q0 + t; };
 #pragma unroll
-  for (int t = 0; t < LPW; ++t)
-    vo[t] = grp == 0
-                ? Opnd<T, A_K>::template offset<B_PLAIN>(q0 + t, lane, p.lda, m0, m_lim, kbeg + 64 * sub)
-                : Opnd<T, B_K>::template offset<MAPB>(q0 + t, lane, p.ldb, n0, p.N, kbeg + 64 * sub);
+  for (int t = 0; t < LPW; ++t) {
+    const int k0 = kbeg + 64 * (sub + sl(t));
+    vo[t] = grp == 0 ? Opnd<T, A_K>::template offset<B_PLAIN>(qt(t), lane, p.lda, m0, m_lim, k0)
+                     : Opnd<T, B_K>::template offset<MAPB>(qt(t), lane, p.ldb, n0, p.N, k0);
+  }
   const bool gk = grp == 0 ? A_K : B_K;
   const uint32_t kbw = gk ? 2u : (uint32_t)((grp == 0 ? p.lda : p.ldb) * 2);
-  lds_t *const dst0 = R0 + (2 * sub + grp) * OPB + q0 * RUN;
+  lds_t *const dst0 = R0 + (2 * sub + grp) * OPB;
+  auto at = [&](int t) { return 2 * sl(t) * OPB + qt(t) * RUN; };
   const bool ragged = (kend - kbeg) % KS != 0;
   auto load = [&](int st) {
     lds_t *d = dst0 + (st & (NST - 1)) * STAGE;
     const uint32_t so = (uint32_t)(st * KS) * kbw;
     if (ragged && st == ns - 1) {  // the stage ends past K: every lane checked
-      const int kr = kend - kbeg - st * KS - 64 * sub;  // valid k of this slice
+      const int kr = kend - kbeg - st * KS - 64 * sub;  // valid k from this wave's first slice
 #pragma unroll
       for (int t = 0; t < LPW; ++t) {
-        const int k = grp == 0 ? Opnd<T, A_K>::run_k(q0 + t, lane) : Opnd<T, B_K>::run_k(q0 + t, lane);
-        dma16(rs, d + t * RUN, k < kr && vo[t] != OOB ? vo[t] + so : OOB);
+        const int k = 64 * sl(t) + (grp == 0 ? Opnd<T, A_K>::run_k(qt(t), lane) : Opnd<T, B_K>::run_k(qt(t), lane));
+        dma16(rs, d + at(t), k < kr && vo[t] != OOB ? vo[t] + so : OOB);
       }
       return;
     }
 #pragma unroll
-    for (int t = 0; t < LPW; ++t) dma16s(rs, d + t * RUN, vo[t], so);
+    for (int t = 0; t < LPW; ++t) dma16s(rs, d + at(t), vo[t], so);
   };
 
-  bf16x8_v fa[2][4], fb[2][4];
-  auto read = [&](int st, bf16x8_v (&a)[4], bf16x8_v (&b)[4]) {
-    const lds_t *t = R0 + (st & (NST - 1)) * STAGE + 2 * (kg >> 1) * OPB;
+  typedef bf16x8_v Frag[QS][FR];
+  Frag fa[2], fb[2];
+  auto read = [&](int st, Frag &a, Frag &b) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = Opnd<T, A_K>::frag(t, 4 * wr + i, kg & 1, lane);
+    for (int q = 0; q < QS; ++q) {
+      const int ks = QS * kg + q;  // k-step of the stage
+      const lds_t *t = R0 + (st & (NST - 1)) * STAGE + 2 * (ks >> 1) * OPB;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) b[j] = Opnd<T, B_K>::frag(t + OPB, 4 * wc + j, kg & 1, lane);
+      for (int i = 0; i < FR; ++i) a[q][i] = Opnd<T, A_K>::frag(t, FR * wr + i, ks & 1, lane);
+#pragma unroll
+      for (int j = 0; j < FR; ++j) b[q][j] = Opnd<T, B_K>::frag(t + OPB, FR * wc + j, ks & 1, lane);
+    }
   };
-  auto multiply = [&](const bf16x8_v (&a)[4], const bf16x8_v (&b)[4]) {
+  auto multiply = [&](const Frag &a, const Frag &b) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int q = 0; q < QS; ++q)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+      for (int i = 0; i < FR; ++i)
+#pragma unroll
+        for (int j = 0; j < FR; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[q][j], a[q][i], acc[i][j], 0, 0, 0);
   };
-  constexpr int NRD = (A_K ? 4 : 8) + (B_K ? 4 : 8);
+  constexpr int NRD = QS * FR * ((A_K ? 1 : 2) + (B_K ? 1 : 2)), NMF = QS * FR * FR;
   // Stage st + 1 has landed for every wave after the barrier, and every wave has
   // its fragments of stage st, whose slot then takes stage st + NST.
-  auto step = [&](int st, bf16x8_v (&a)[4], bf16x8_v (&b)[4], bf16x8_v (&an)[4], bf16x8_v (&bn)[4]) {
+  auto step = [&](int st, Frag &a, Frag &b, Frag &an, Frag &bn) {
     const int later = ns - 2 - st;  // stages after st + 1, in flight at most NST - 2
     if (later >= NST - 2) wait_barrier<(NST - 2) * LPW>();
     else if (later == 1) wait_barrier<LPW>();
@@ -190,7 +216,7 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
     if (st + NST < ns) load(st + NST);
     read(st + 1, an, bn);  // (after the last stage: another slot's stale data, unused)
     multiply(a, b);
-    interleave_steps<NRD, 16>();
+    interleave_steps<NRD, NMF>();
     __builtin_amdgcn_sched_barrier(0);
   };
   static_assert(NST == 4, "the waits above");
@@ -207,8 +233,8 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
   }
 
   // ------------------------------------------------------------ epilogue
-  // Every wave writes its partial 64 x 64 block to its k-step's copy of the fp32
-  // tile in the (now idle) ring, 16-byte chunk c of row r at chunk c ^ (r & 15);
+  // Every wave writes its partial block to its k-steps' copy of the fp32 tile in the
+  // (now idle) ring, 16-byte chunk c of row r at chunk c ^ (r & 15) (& 7: 32 tile);
   // then each thread adds the copies of four columns (a pair of fours for RoPE
   // and SwiGLU) in k-step order and stores them, whole rows by consecutive lanes.
   // Tensors the epilogue reads are loaded before the barrier.
@@ -218,11 +244,12 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
   typedef __attribute__((address_space(3))) f32x4_v lds_f4;
   constexpr bool PAIR = EPI == LC_EPI_ROPE || SWI;
   constexpr int QW = PAIR ? T / 8 : T / 4;   // column quads a row's threads take
-  constexpr int IT = T * QW / NT;
+  constexpr int IT = T * QW > NT ? T * QW / NT : 1;  // (RoPE, SwiGLU, 32 tile: half the threads)
+  constexpr int SWZ = T / 4 < 16 ? T / 4 - 1 : 15;
   constexpr bool LD = EPI == LC_EPI_RESIDUAL || EPI == LC_EPI_ACCUM_F32 || EPI == LC_EPI_SWIGLU_BWD;
   const int q = tid % QW;
   int n;  // first of this thread's columns
-  if constexpr (EPI == LC_EPI_ROPE && T == 64) n = (n0 & ~127) + (n0 & 64) / 2 + 4 * q;
+  if constexpr (EPI == LC_EPI_ROPE && T < 128) n = (n0 & ~127) + (n0 & (128 - T)) / 2 + 4 * q;
   else n = n0 + 4 * q;
   const bool n_ok = n < p.N;
   auto row_of = [&](int it) { return (it * NT + tid) / QW; };
@@ -244,15 +271,15 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
   __syncthreads();  // every wave's last fragment reads are done
   lds_t *const E = R0 + kg * (T * T * 4);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < FR; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = 64 * wr + 16 * i + (lane & 15), c = 16 * wc + 4 * j + (lane >> 4);
-      *reinterpret_cast<lds_f4 *>(E + r * (T * 4) + ((c ^ (r & 15)) << 4)) = acc[i][j];
+    for (int j = 0; j < FR; ++j) {
+      const int r = 16 * (FR * wr + i) + (lane & 15), c = 4 * (FR * wc + j) + (lane >> 4);
+      *reinterpret_cast<lds_f4 *>(E + r * (T * 4) + ((c ^ (r & SWZ)) << 4)) = acc[i][j];
     }
   __syncthreads();
   auto sum4 = [&](int r, int c) {
-    const lds_t *s = R0 + r * (T * 4) + ((c ^ (r & 15)) << 4);
+    const lds_t *s = R0 + r * (T * 4) + ((c ^ (r & SWZ)) << 4);
     f32x4_v v = *reinterpret_cast<const lds_f4 *>(s);
 #pragma unroll
     for (int k = 1; k < C::KSPL; ++k) v += *reinterpret_cast<const lds_f4 *>(s + k * (T * T * 4));
@@ -261,7 +288,7 @@ __global__ __launch_bounds__(T * 4) void gemm_tile_kernel(GemmP p) {
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     const int r = row_of(it), m = m0 + r;
-    if (m >= m_lim || !n_ok) continue;
+    if (r >= T || m >= m_lim || !n_ok) continue;
     const f32x4_v v = sum4(r, q);
     const int64_t oc = (int64_t)m * p.ldc + n;
     if constexpr (PAIR) {
@@ -325,9 +352,11 @@ lc_status launch_t(const GemmP &p, int tile, hipStream_t s) {
   if (p.gmode == LC_GROUP_ROWS) grid = (unsigned)(p.tiles_m + p.ngroups) * (unsigned)p.tiles_n;
   if (p.gmode == LC_GROUP_K) grid *= (unsigned)p.ngroups;
   if (tile == 128)
-    hipLaunchKernelGGL((gemm_tile_kernel<128, A_K, B_K, EPI, TM>), dim3(grid), dim3(512), 0, s, p);
+    hipLaunchKernelGGL((gemm_tile_kernel<128, A_K, B_K, EPI, TM>), dim3(grid), dim3(threads(128)), 0, s, p);
+  else if (tile == 64)
+    hipLaunchKernelGGL((gemm_tile_kernel<64, A_K, B_K, EPI, TM>), dim3(grid), dim3(threads(64)), 0, s, p);
   else
-    hipLaunchKernelGGL((gemm_tile_kernel<64, A_K, B_K, EPI, TM>), dim3(grid), dim3(256), 0, s, p);
+    hipLaunchKernelGGL((gemm_tile_kernel<32, A_K, B_K, EPI, TM>), dim3(grid), dim3(threads(32)), 0, s, p);
   return check_launch("gemm_tile_kernel");
 }
 

@@ -1,4 +1,4 @@
-"""The bf16 GEMM's output tiles (256, 128 and 64, chosen by the output's size)
+"""The bf16 GEMM's output tiles (256, 128, 64 and 32, chosen by the output's size)
 at the edges of tiles, rings and k-steps: every layout and epilogue against
 float64 products of the same operands. Integer-valued operands make the plain
 products exact in fp32 (|sum| < 2^24), so those are compared bit for bit."""
@@ -12,12 +12,12 @@ from tests.gpu_util import DEV, banner
 pytestmark = pytest.mark.gpu
 
 BF16, FP32, FP16 = lc.LC_BF16, lc.LC_FP32, lc.LC_FP16
-# (M, N): 64 tiles, 128 tiles (over 256 of 64, ragged both ways; m/n-major rows
-# need a multiple of 8), 256 tiles
-SIZES = [(1, 8), (72, 136), (1096, 1928), (1480, 6152)]
-# stages of 128 (64 tile) or 64 (128, 256): none full, one, the ring's wrap, a
+# (M, N): 32 tiles, 64 tiles, 128 tiles (over 256 of 64, ragged both ways; m/n-major
+# rows need a multiple of 8), 256 tiles
+SIZES = [(1, 8), (72, 136), (520, 712), (1096, 1928), (1480, 6152)]
+# stages of 256 (32 tile), 128 (64 tile) or 64 (128, 256): none full, one, the ring's wrap, a
 # ragged last stage
-DEPTHS = [8, 128, 200, 520, 1032]
+DEPTHS = [8, 128, 200, 520, 1032, 2056]
 
 
 def ints(g, *shape):
@@ -56,7 +56,7 @@ def rel(got, ref):
     return float((got.double() - ref).norm() / ref.norm())
 
 
-@pytest.mark.parametrize("T,f,d", [(40, 64, 264), (1003, 960, 136), (2056, 3136, 72)])
+@pytest.mark.parametrize("T,f,d", [(40, 64, 264), (520, 320, 520), (1003, 960, 136), (2056, 3136, 72)])
 def test_tiles_swiglu_and_residual(T, f, d):
     """Gate/up with SwiGLU, down with the residual and the SwiGLU backward. The
     sums are exact, so gate and up are too; bf16 outputs are one rounding off
@@ -88,7 +88,7 @@ def test_tiles_swiglu_and_residual(T, f, d):
     assert rel(da[:, f:], dact * gr * sg) < 2 ** -9
 
 
-@pytest.mark.parametrize("T,H,seq", [(40, 1, 8), (1003, 5, 59), (1480, 16, 1480)])
+@pytest.mark.parametrize("T,H,seq", [(40, 1, 8), (520, 2, 130), (1003, 5, 59), (1480, 16, 1480)])
 def test_tiles_rope(T, H, seq):
     """q|k|v of H heads each, q and k rotated, with the bf16 copy."""
     banner(f"gemm tiles rope T={T} H={H}")
@@ -111,8 +111,8 @@ def test_tiles_rope(T, H, seq):
     assert rel(qb.view(T, 3 * H, 128), ref) < 2 ** -8
 
 
-@pytest.mark.parametrize("sizes,N", [([300, 0, 17, 512, 256, 1], 264), ([900, 40, 0, 700], 1416)],
-                         ids=["64", "128"])
+@pytest.mark.parametrize("sizes,N", [([30, 0, 50, 1], 72), ([300, 0, 17, 512, 256, 1], 264),
+                                     ([900, 40, 0, 700], 1416)], ids=["32", "64", "128"])
 def test_tiles_grouped(sizes, N):
     banner(f"gemm tiles grouped {sizes} N={N}")
     g = gen(N)
