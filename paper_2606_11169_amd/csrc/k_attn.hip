@@ -253,8 +253,8 @@ struct AttnP {
 // XCDs round-robin, so each XCD receives blocks of every size; with the block
 // index fastest instead, one XCD would receive only the heaviest and the
 // middle blocks of every head (twice the mean work).
-__device__ __forceinline__ void query_block_of(const AttnP &p, int nqb, int &qb, int &h, int &b) {
-  const int nbh = p.H * p.B, i = (int)blockIdx.x;
+__device__ __forceinline__ void query_block_of(const AttnP &p, int i, int nqb, int &qb, int &h, int &b) {
+  const int nbh = p.H * p.B;
   qb = nqb - 1 - i / nbh;
   h = (i % nbh) % p.H;
   b = (i % nbh) / p.H;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_kernel(AttnP p) {
   __shared__ __align__(16) char smem[KG * 2 * 2 * TILE];  // per group, stage s: K tile | V tile
   const int nqb = (p.S + QROWS - 1) / QROWS;
   int qb, h, b;
-  query_block_of(p, nqb, qb, h, b);
+  query_block_of(p, (int)blockIdx.x, nqb, qb, h, b);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
@@ -503,17 +503,18 @@ __device__ __forceinline__ void store_row_t(__bf16 *row, const f32x16_v (&acc)[4
 // KG = 2 (grids smaller than two workgroups per compute unit, as in the forward):
 // 128 queries, waves w and w + 4 own the same 32 and take the two halves of every
 // key block; their sums are added through LDS (16 heads of 2048: 95 -> 69 us).
-template <typename QE, int KG>
-__global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(AttnP p) {
+template <typename QE> constexpr int dq_smem() { return 2 * (std::is_same<QE, __bf16>::value ? 2 : 3) * TILE; }
+// One workgroup's part: query block `index` of the grid's order; HAVE_D: D and
+// -lse log2(e) are written already.
+template <typename QE, int KG, bool HAVE_D>
+__device__ __forceinline__ void dq_block(const AttnP &p, int index, lds_t *const L) {
   typedef typename V8<QE>::type QV;
   constexpr bool SEP = !std::is_same<QE, __bf16>::value;  // separate bf16 K tile
   constexpr int NTQ = SEP ? 3 : 2;                          // tiles per stage
   constexpr int QROWS = ROWS / KG, NJ = 2 / KG;             // queries; 32-key blocks per wave
-  __shared__ __align__(16) char smem[2 * NTQ * TILE];
-  lds_t *const L = LDS_AS(char, smem);
   const int nqb = (p.S + QROWS - 1) / QROWS;
   int qb, h, b;
-  query_block_of(p, nqb, qb, h, b);
+  query_block_of(p, index, nqb, qb, h, b);
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
@@ -567,6 +568,9 @@ __global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(AttnP p) {
   // D of this query (its O row read while the first block streams in): the
   // lane's 64 products, then its partner's (lane ^ 32)
   float Dq = 0.0f;
+  if constexpr (HAVE_D) {
+    Dq = p.D[si];
+  } else {
   if (active) {
 #pragma unroll
     for (int es = 0; es < 8; ++es) {
@@ -580,6 +584,7 @@ __global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(AttnP p) {
   if (active && hf == 0 && kg == 0) {
     p.D[si] = Dq;
     p.nl2[si] = -lse2;
+  }
   }
   wait_vm0();
   __syncthreads();
@@ -670,6 +675,12 @@ __global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(AttnP p) {
   store_row_t(p.dq + h * HD + (row0 + myq) * p.ld_d, acc, 1.0f, hf);
 }
 
+template <typename QE, int KG>
+__global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(AttnP p) {
+  __shared__ __align__(16) char smem[dq_smem<QE>()];
+  dq_block<QE, KG, false>(p, (int)blockIdx.x, LDS_AS(char, smem));
+}
+
 // dK, dV: one workgroup of 8 waves per 128 keys and query head. Waves w and
 // w + 4 own the same 32 keys (their K and V fragments stay in registers) and
 // take the first and the second 32 queries of every 64-query block at or
@@ -680,21 +691,23 @@ __global__ __launch_bounds__(NT) void attn_bwd_dq_kernel(AttnP p) {
 // grouped-query attention the workgroup writes its query head's share of the
 // key/value head's dK, dV as fp32 rows; attn_gqa_sum_kernel adds the shares.
 constexpr int KV_ROWS = 128;
+// two stages (256-byte aligned for frag_cols_x), reused at the end for the
+// partial dK, dV that waves 4-7 hand over (4 x 128 rows x 64 lanes fp32)
+template <typename QE> constexpr int dkdv_stage() { return (std::is_same<QE, __bf16>::value ? 2 : 3) * TILE + 512; }
+template <typename QE> constexpr int dkdv_smem() {
+  constexpr int handoff = 4 * 128 * 64 * 4;
+  return 2 * dkdv_stage<QE>() > handoff ? 2 * dkdv_stage<QE>() : handoff;
+}
+// One workgroup's part: key block kblk of query head h, batch row b.
 template <typename QE>
-__global__ __launch_bounds__(NT) void attn_bwd_dkdv_kernel(AttnP p) {
+__device__ __forceinline__ void dkdv_block(const AttnP &p, int kblk, int h, int b, char *const smem) {
   typedef typename V8<QE>::type QV;
   constexpr bool SEP = !std::is_same<QE, __bf16>::value;  // separate bf16 Q tile
   constexpr int NTK = SEP ? 3 : 2;                          // row tiles per stage
   constexpr int RPW = SEP ? 8 : 4;                          // tile runs per wave
-  constexpr int STAGE = NTK * TILE + 512;
-  // two stages (256-byte aligned for frag_cols_x), reused at the end for the
-  // partial dK, dV that waves 4-7 hand over (4 x 128 rows x 64 lanes fp32)
-  constexpr int HANDOFF = 4 * 128 * 64 * 4;
-  __shared__ __align__(256) char smem[2 * STAGE > HANDOFF ? 2 * STAGE : HANDOFF];
+  constexpr int STAGE = dkdv_stage<QE>();
   lds_t *const L = LDS_AS(char, smem);
-  const int kblk = (int)blockIdx.x / p.H, h = (int)blockIdx.x % p.H;  // earliest (heaviest) keys first
   const int kvh = h / p.G;
-  const int b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int pw = w & 3, hq = w >> 2;  // key block of the pair, query half
@@ -880,6 +893,57 @@ __global__ __launch_bounds__(NT) void attn_bwd_dkdv_kernel(AttnP p) {
   }
 }
 
+template <typename QE>
+__global__ __launch_bounds__(NT) void attn_bwd_dkdv_kernel(AttnP p) {
+  __shared__ __align__(256) char smem[dkdv_smem<QE>()];
+  // earliest (heaviest) keys first
+  dkdv_block<QE>(p, (int)blockIdx.x / p.H, (int)blockIdx.x % p.H, (int)blockIdx.y, smem);
+}
+
+// D = rowsum(dO * O) and -lse log2(e) of every query and head: 16 lanes per head
+// row of 128 values
+__global__ __launch_bounds__(256) void attn_bwd_d_kernel(AttnP p) {
+  const int64_t n = (int64_t)p.B * p.S * p.H;
+  const int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);  // (row, head), heads fastest
+  const int l = threadIdx.x & 15;
+  const int64_t row = min(i, n - 1) / p.H, at = row * p.ld_o + (min(i, n - 1) % p.H) * HD + 8 * l;
+  const bf16x8_v a = *reinterpret_cast<const bf16x8_v *>(p.dout + at);
+  const bf16x8_v o = *reinterpret_cast<const bf16x8_v *>(p.o + at);
+  float d = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) d += (float)a[e] * (float)o[e];
+#pragma unroll
+  for (int m = 8; m > 0; m >>= 1) d += __shfl_xor(d, m, 64);
+  if (l == 0 && i < n) {
+    const int64_t si = (row / p.S * p.H + i % p.H) * p.S + row % p.S;
+    p.D[si] = d;
+    p.nl2[si] = -(p.lse[si] * LOG2E);
+  }
+}
+
+// dQ (128 queries per workgroup, KG = 2) and dK/dV in one grid, for grids of at most
+// one workgroup of each per compute unit, which would last as long as their longest
+// causal block one after the other: eight blocks of the one, eight of the other (one per XCD), each list
+// heaviest first, so that the one's short blocks fill the chip beside the other's
+// long ones. D and -lse log2(e) are written before by attn_bwd_d_kernel. Backward of
+// 4 heads of 256: 36 -> 21 us, 16 heads of 2048 (256 blocks each) 116 -> 93; with
+// more blocks each list evens itself out and the extra pass is lost (16 heads of 2 x
+// 1920, 480 blocks: 159 -> 169).
+template <typename QE>
+__global__ __launch_bounds__(NT) void attn_bwd_both_kernel(AttnP p) {
+  constexpr int BYTES = dkdv_smem<QE>() > dq_smem<QE>() ? dkdv_smem<QE>() : dq_smem<QE>();
+  __shared__ __align__(256) char smem[BYTES];
+  const int i = (int)blockIdx.x, n = p.S / KV_ROWS * p.H * p.B;  // blocks of each list
+  const int idx = (i >> 4) * 8 + (i & 7);
+  if (idx >= n) return;
+  if ((i >> 3) & 1) {
+    dq_block<QE, 2, true>(p, idx, LDS_AS(char, smem));
+  } else {
+    const int bh = p.H * p.B;
+    dkdv_block<QE>(p, idx / bh, idx % bh % p.H, idx % bh / p.H, smem);
+  }
+}
+
 // Grouped-query attention: dk, dv of key/value head kvh = the sum, in head
 // order, of the fp32 shares of its G query heads (8 elements per thread)
 __global__ __launch_bounds__(256) void attn_gqa_sum_kernel(AttnP p) {
@@ -1037,7 +1101,7 @@ lc_status check_extents(const lc_attn_args &a) {
   return LC_OK;
 }
 
-// Fewer than two 256-query workgroups per compute unit (forward and dQ): the KG = 2
+// Fewer than two 256-query workgroups per compute unit (forward, dQ): the KG = 2
 // kernels' smaller workgroups. From two on, the heavy blocks first and the light
 // ones after them fill the chip evenly.
 bool small_grid(unsigned blocks) { return blocks < 512; }
@@ -1062,16 +1126,25 @@ lc_status bwd_mc(const lc_attn_args &a, hipStream_t s) {
     hipLaunchKernelGGL(attn_bwd_copy_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, p);
     LC_TRY(check_launch("attn_bwd_copy_kernel"));
   }
-  // dQ first: it writes D, which the dK/dV kernel reads
   const unsigned bh = (unsigned)(a.H * a.B), nb = (unsigned)((a.S + ROWS - 1) / ROWS);
-  if (small_grid(nb * bh))
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<QE, 2>), dim3((unsigned)(a.S / QB) * bh), dim3(NT), 0, s, p);
-  else
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<QE, 1>), dim3(nb * bh), dim3(NT), 0, s, p);
-  LC_TRY(check_launch("attn_bwd_dq_kernel"));
-  hipLaunchKernelGGL(attn_bwd_dkdv_kernel<QE>, dim3((unsigned)(a.S / KV_ROWS * a.H), a.B), dim3(NT), 0,
-                     s, p);
-  LC_TRY(check_launch("attn_bwd_dkdv_kernel"));
+  const unsigned n = (unsigned)(a.S / KV_ROWS) * bh;  // blocks of 128 keys, and of 128 queries
+  if (n <= 256) {
+    const int64_t rows = (int64_t)a.B * a.S * a.H;
+    hipLaunchKernelGGL(attn_bwd_d_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s, p);
+    LC_TRY(check_launch("attn_bwd_d_kernel"));
+    hipLaunchKernelGGL(attn_bwd_both_kernel<QE>, dim3((n + 7) / 8 * 16), dim3(NT), 0, s, p);
+    LC_TRY(check_launch("attn_bwd_both_kernel"));
+  } else {
+    // dQ first: it writes D, which the dK/dV kernel reads
+    if (small_grid(nb * bh))
+      hipLaunchKernelGGL((attn_bwd_dq_kernel<QE, 2>), dim3(n), dim3(NT), 0, s, p);
+    else
+      hipLaunchKernelGGL((attn_bwd_dq_kernel<QE, 1>), dim3(nb * bh), dim3(NT), 0, s, p);
+    LC_TRY(check_launch("attn_bwd_dq_kernel"));
+    hipLaunchKernelGGL(attn_bwd_dkdv_kernel<QE>, dim3((unsigned)(a.S / KV_ROWS * a.H), a.B), dim3(NT), 0,
+                       s, p);
+    LC_TRY(check_launch("attn_bwd_dkdv_kernel"));
+  }
   if (p.G > 1) {
     const int64_t n8 = (int64_t)a.B * a.S * p.Hkv * HD / 8;
     hipLaunchKernelGGL(attn_gqa_sum_kernel, dim3((unsigned)((n8 + 255) / 256)), dim3(256), 0, s, p);

@@ -1,5 +1,6 @@
-"""The attention kernels' two workgroup shapes (256 queries; 128 queries with the
-keys split over two wave groups, for grids under 512 blocks) at sequence lengths
+"""The attention kernels' workgroup shapes (256 queries; 128 queries with the
+keys split over two wave groups, for grids under 512 blocks; dQ and dK/dV in one grid
+up to 256 blocks of each) at sequence lengths
 whose last block is half full and whose first block leaves the second group
 without a visible key: against float64 of the same fp16/bf16 q, k, v."""
 import math
@@ -18,7 +19,8 @@ def rel(got, ref):
 
 
 @pytest.mark.parametrize("dt", ["fp16", "bf16"])
-@pytest.mark.parametrize("B,S,H,kv", [(1, 128, 1, 1), (2, 384, 2, 1), (1, 1152, 3, 3), (8, 384, 32, 32),
+@pytest.mark.parametrize("B,S,H,kv", [(1, 128, 1, 1), (2, 384, 2, 1), (1, 1152, 3, 3), (2, 1152, 16, 4),
+                                      (8, 384, 32, 32),
                                       (16, 256, 32, 8)])
 def test_both_shapes(B, S, H, kv, dt):
     banner(f"attention grids B={B} S={S} H={H}/{kv} {dt}")
