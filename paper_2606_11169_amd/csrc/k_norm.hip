@@ -5,10 +5,10 @@
 //             dx_tk = dres_tk + rstd_t (dxh_tk - xh_tk * mean_k(dxh*xh)),
 //             dg_k += sum_t dn_tk xh_tk
 //
-// Forward: one wave per row, 8 elements per lane per step (16- or 32-byte
-// accesses); rows of up to 4096 elements stay in registers between the row's
-// reduction and its write (one read), longer rows are read twice (the second
-// read hits L2). Backward: rows of up to 8192 elements stay in registers, split
+// Forward: 8 elements per lane per step (16- or 32-byte accesses); rows of up to
+// 4096 elements stay in one wave's registers between the row's
+// reduction and its write, up to 8192 in two waves'; longer rows are read twice (the
+// second read hits L2; 3001 rows of 5120: 24 us that way, 20 in registers). Backward: rows of up to 8192 elements stay in registers, split
 // over one to eight waves by their length; longer rows go one per wave, read
 // twice (3001 rows of 5120: 134 us that way with its own partial-sum pass, 67 in
 // registers). Every tensor's element type is a run-time
@@ -27,7 +27,7 @@
 namespace lc {
 namespace {
 
-constexpr int ROWS_PER_BLOCK = 4;  // forward: one wave per row
+constexpr int ROWS_PER_BLOCK = 4;  // forward: rows of one wave each
 constexpr int MAXU = 8;            // 8-element chunks per lane held in registers
 constexpr int MAXD = 64 * 8 * MAXU;  // longest row the forward keeps in registers
 constexpr int MAXB = 8192;           // longest row the backward keeps in registers
@@ -46,30 +46,43 @@ struct NormP {
   int nblk;
 };
 
-template <int XDT, int WDT, int ODT>
+// WPR waves per row (a power of two): one up to MAXD values, two up to MAXB; longer
+// rows go one per wave, read twice.
+template <int WPR, int XDT, int WDT, int ODT>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(NormP p) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * ROWS_PER_BLOCK + (threadIdx.x >> 6);
-  if (row >= p.rows) return;
+  __shared__ float part[4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t row = (int64_t)blockIdx.x * (ROWS_PER_BLOCK / WPR) + wv / WPR;
+  if (WPR == 1 && row >= p.rows) return;
   const int64_t base = row * p.d;
+  const bool ok = row < p.rows;
   float ss = 0.0f;
-  if (p.d <= MAXD) {
+  if (WPR > 1 || p.d <= MAXD) {
+    const int l = (wv % WPR) * 64 + lane;  // lane of the row
     float v[MAXU][8];
 #pragma unroll
     for (int u = 0; u < MAXU; ++u) {
-      const int c = lane * 8 + 512 * u;
-      if (c < p.d) {
+      const int c = l * 8 + 512 * WPR * u;
+      if (ok && c < p.d) {
         ld8<XDT>(p.x, base + c, p.x_dt, v[u]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) ss += v[u][e] * v[u][e];
       }
     }
     ss = wave_sum(ss);
+    if constexpr (WPR > 1) {
+      if (lane == 0) part[wv] = ss;
+      __syncthreads();
+      ss = part[wv / WPR * WPR];
+#pragma unroll
+      for (int w = 1; w < WPR; ++w) ss += part[wv / WPR * WPR + w];
+      if (!ok) return;
+    }
     const float r = 1.0f / sqrtf(ss / (float)p.d + p.eps);
-    if (lane == 0) p.rstd[row] = r;
+    if (l == 0) p.rstd[row] = r;
 #pragma unroll
     for (int u = 0; u < MAXU; ++u) {
-      const int c = lane * 8 + 512 * u;
+      const int c = l * 8 + 512 * WPR * u;
       if (c < p.d) {
         float gv[8];
         ld8<WDT>(p.g, c, p.w_dt, gv);
@@ -338,21 +351,25 @@ NormP make_params(const lc_norm_args &a) {
 
 }  // namespace
 
+template <int XDT, int WDT, int ODT>
+static void fwd_typed(const NormP &p, hipStream_t s) {
+  const bool two = p.d > MAXD && p.d <= MAXB;
+  const int rows = two ? ROWS_PER_BLOCK / 2 : ROWS_PER_BLOCK;
+  const dim3 grid((unsigned)((p.rows + rows - 1) / rows));
+  if (two) hipLaunchKernelGGL((rmsnorm_fwd_kernel<2, XDT, WDT, ODT>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((rmsnorm_fwd_kernel<1, XDT, WDT, ODT>), grid, dim3(256), 0, s, p);
+}
+
 lc_status rmsnorm_fwd_launch(const lc_norm_args &a, hipStream_t s) {
   LC_TRY(check_common(a, false));
   const NormP p = make_params(a);
-  const dim3 grid((unsigned)((a.T + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK));
   // the stages' type mixes (bf16: gain and output bf16, rows fp32 or, in the first
   // layer, bf16; fp32: all fp32) have their own instantiations; every other mix
   // takes the generic kernel
-  if (p.x_dt == LC_FP32 && p.w_dt == LC_BF16 && p.out_dt == LC_BF16)
-    hipLaunchKernelGGL((rmsnorm_fwd_kernel<LC_FP32, LC_BF16, LC_BF16>), grid, dim3(256), 0, s, p);
-  else if (p.x_dt == LC_BF16 && p.w_dt == LC_BF16 && p.out_dt == LC_BF16)
-    hipLaunchKernelGGL((rmsnorm_fwd_kernel<LC_BF16, LC_BF16, LC_BF16>), grid, dim3(256), 0, s, p);
-  else if (p.x_dt == LC_FP32 && p.w_dt == LC_FP32 && p.out_dt == LC_FP32)
-    hipLaunchKernelGGL((rmsnorm_fwd_kernel<LC_FP32, LC_FP32, LC_FP32>), grid, dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL((rmsnorm_fwd_kernel<-1, -1, -1>), grid, dim3(256), 0, s, p);
+  if (p.x_dt == LC_FP32 && p.w_dt == LC_BF16 && p.out_dt == LC_BF16) fwd_typed<LC_FP32, LC_BF16, LC_BF16>(p, s);
+  else if (p.x_dt == LC_BF16 && p.w_dt == LC_BF16 && p.out_dt == LC_BF16) fwd_typed<LC_BF16, LC_BF16, LC_BF16>(p, s);
+  else if (p.x_dt == LC_FP32 && p.w_dt == LC_FP32 && p.out_dt == LC_FP32) fwd_typed<LC_FP32, LC_FP32, LC_FP32>(p, s);
+  else fwd_typed<-1, -1, -1>(p, s);
   return check_launch("rmsnorm_fwd_kernel");
 }
 
