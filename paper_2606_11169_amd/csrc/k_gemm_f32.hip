@@ -24,7 +24,7 @@
 namespace lc {
 namespace {
 
-constexpr int NW = 4;    // waves: shares of k
+constexpr int NW = 4;    // waves: shares of k (the ring's 32 tile also with 8)
 constexpr int KW = 32;   // k per wave and step
 
 struct F32P {
@@ -66,9 +66,9 @@ __device__ __forceinline__ int column(const F32P &p, int tn, int j, int *n, bool
   return *n;
 }
 
-// The waves' partial tiles added in wave order and the epilogue. `part`: NW
+// The waves' partial tiles added in wave order and the epilogue. `part`: W
 // tiles of T rows of T + 1 floats of LDS that no wave reads any more.
-template <int T>
+template <int T, int W>
 __device__ __forceinline__ void finish(const F32P &p, float *part, const f32x16_v (&acc)[T / 32][T / 32], int m0,
                                        int tn, int w, int lane) {
   constexpr int F = T / 32, LD = T + 1;
@@ -85,7 +85,7 @@ __device__ __forceinline__ void finish(const F32P &p, float *part, const f32x16_
   auto sum = [&](int r, int c) {
     float v = part[r * LD + c];
 #pragma unroll
-    for (int i = 1; i < NW; ++i) v += part[i * T * LD + r * LD + c];
+    for (int i = 1; i < W; ++i) v += part[i * T * LD + r * LD + c];
     return v;
   };
   const bool pair = p.epi == LC_EPI_SWIGLU || p.epi == LC_EPI_ROPE;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void finish(const F32P &p, float *part, const f32x16_
   bool ok;
   column<T>(p, tn, j, &n, &ok);
   if (!ok) return;
-  for (int r = tid / cols; r < T; r += 64 * NW / cols) {
+  for (int r = tid / cols; r < T; r += 64 * W / cols) {
     const int m = m0 + r;
     if (m >= p.M) break;
     const float v = sum(r, j);
@@ -178,19 +178,21 @@ struct Slice {
 
 constexpr int NST = 4;  // stages of the ring
 
-// SUB slices per stage; every wave multiplies 32 SUB / 4 k of each stage
-template <int T, bool A_K, bool B_K>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_ring_kernel(F32P p) {
-  constexpr int F = T / 32, SUB = 64 / T, KS = 32 * SUB, G = SUB;  // G: groups of 8 k per wave and stage
+// SUB slices per stage; each of the W waves multiplies 8 G k of every stage. Eight
+// waves halve a tile's chain of products (two waves per SIMD instead of one; tiny step
+// 850 -> 797 us).
+template <int T, int W, bool A_K, bool B_K>
+__global__ __launch_bounds__(64 * W) void gemm_f32_ring_kernel(F32P p) {
+  constexpr int F = T / 32, SUB = 64 / T * (W / 4), KS = 32 * SUB, G = 64 / T;
   constexpr int OPB = Slice<T, true>::BYTES, STAGE = 2 * SUB * OPB;
-  constexpr int LPW = 2 * SUB * (T / 8) / NW;  // loads per wave and stage: A by waves 0, 1, B by 2, 3
-  constexpr int PART = NW * T * (T + 1) * 4;
-  static_assert(KS == NW * 8 * G && LPW == 4, "");
+  constexpr int LPW = 2 * SUB * (T / 8) / W;  // loads per wave and stage: A by the first half of the waves
+  constexpr int PART = W * T * (T + 1) * 4;
+  static_assert(KS == W * 8 * G && LPW == 4, "");
   __shared__ __align__(16) char ring[NST * STAGE > PART ? NST * STAGE : PART];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = (int)(blockIdx.x / p.tiles_n) * T, tn = (int)(blockIdx.x % p.tiles_n);
-  const int grp = w >> 1, wo = w & 1;
+  const int grp = w / (W / 2), wo = w % (W / 2);
   const i32x4_v rs = grp == 0 ? make_rsrc(p.A, p.a_bytes) : make_rsrc(p.B, p.b_bytes);
   const bool gk = grp == 0 ? A_K : B_K;
   const int64_t ld = grp == 0 ? p.lda : p.ldb;
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_ring_kernel(F32P p) {
     if (st + 1 < ns) step(st + 1, fa[1], fb[1], fa[0], fb[0]);
   }
   __syncthreads();  // every wave's last fragment reads are done
-  finish<T>(p, reinterpret_cast<float *>(ring), acc, m0, tn, w, lane);
+  finish<T, W>(p, reinterpret_cast<float *>(ring), acc, m0, tn, w, lane);
 }
 
 // ------------------------------------------------------------------ registers
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(F32P p) {
     if (k + 2 * STEP < p.K) load(k + 2 * STEP, a[0], b[0]);
     multiply(a[1], b[1]);
   }
-  finish<T>(p, part, acc, m0, tn, w, lane);
+  finish<T, NW>(p, part, acc, m0, tn, w, lane);
 }
 
 template <int T>
@@ -384,10 +386,17 @@ lc_status run_f32(F32P p, bool ak, bool bk, bool ring, hipStream_t s) {
   p.tiles_n = (unsigned)tn;
   const dim3 grid((unsigned)(tm * tn)), block(64 * NW);
   if (ring) {
-    if (ak && bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, true, true>), grid, block, 0, s, p);
-    else if (ak) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, true, false>), grid, block, 0, s, p);
-    else if (bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, false, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((gemm_f32_ring_kernel<T, false, false>), grid, block, 0, s, p);
+    auto launch = [&](auto w) {
+      constexpr int W = decltype(w)::value;
+      const dim3 blk(64 * W);
+      if (ak && bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, true, true>), grid, blk, 0, s, p);
+      else if (ak) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, true, false>), grid, blk, 0, s, p);
+      else if (bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, false, true>), grid, blk, 0, s, p);
+      else hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, false, false>), grid, blk, 0, s, p);
+    };
+    // (eight waves' stages take a compute unit's LDS for one workgroup)
+    if (T == 32 && tm * tn <= 256) launch(std::integral_constant<int, T == 32 ? 8 : 4>{});
+    else launch(std::integral_constant<int, 4>{});
     return check_launch("gemm_f32_ring_kernel");
   }
   if (ak && bk) hipLaunchKernelGGL((gemm_f32_kernel<T, true, true>), grid, block, 0, s, p);
