@@ -133,6 +133,9 @@ inline unsigned ceil_div(size_t a, size_t b) { return unsigned((a + b - 1) / b);
 // ------------------------------------------------------------------ internal launchers
 // Defined in the kernel translation units; used by the stage composer.
 lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s);
+// x then w, in one launch where both are small (independent products: x an input
+// gradient, w a weight gradient)
+lc_status gemm_pair_launch(const lc_gemm_args &x, const lc_gemm_args &w, hipStream_t s);
 lc_status zero_fill_launch(float *buf, size_t n, hipStream_t s);
 lc_status rmsnorm_fwd_launch(const lc_norm_args &a, hipStream_t s);
 lc_status rmsnorm_bwd_launch(const lc_norm_args &a, hipStream_t s);

@@ -114,8 +114,8 @@ struct EpiTypes {
   static constexpr int X = TM == 0 ? -1 : SWI ? LC_FP32 : ROPE ? LC_BF16 : -1;
 };
 
-// Where a workgroup's tile lies: false when it has none (uniform across the
-// workgroup). Workgroups are dispatched round-robin over the 8 XCDs; each XCD
+// Where the tile of workgroup wg of nwg lies: false when it has none (uniform across
+// the workgroup). Workgroups are dispatched round-robin over the 8 XCDs; each XCD
 // gets a contiguous run of tiles, walked in groups of p.group tile-rows
 // (chosen by the host) so that neighbouring workgroups share A rows and B
 // columns in the XCD's L2.
@@ -127,9 +127,7 @@ struct Tile {
   void *C;
 };
 template <int BM>
-__device__ __forceinline__ bool find_tile(const GemmP &p, Tile &t) {
-  int wg = blockIdx.x;
-  const int nwg = gridDim.x;
+__device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile &t) {
   if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
   t.m_lim = p.M;
   t.kbeg = 0;
@@ -172,7 +170,13 @@ __device__ __forceinline__ bool find_tile(const GemmP &p, Tile &t) {
 }  // namespace
 
 // k_gemm_tile.hip: the products whose grid of 256 x 256 tiles would leave most
-// of the chip idle (tile = 128 or 64)
+// of the chip idle (tile = 128, 64 or 32)
 lc_status gemm_tile_launch(GemmP p, const lc_gemm_args &a, int tile, hipStream_t s);
+// Two products of tiles 32 or 64 in one launch: x an input gradient (A k-major, B
+// not; STORE, or SWIGLU_BWD with the stage's types), w a weight gradient (neither
+// k-major; ACCUM_F32).
+lc_status gemm_tile_pair_launch(GemmP x, int x_epi, int x_tile, GemmP w, int w_tile, hipStream_t s);
+// The fp32 pair: LC_OK and *done set if both take the ring's eight-wave 32 tile.
+lc_status gemm_f32_pair_launch(const lc_gemm_args &x, const lc_gemm_args &w, hipStream_t s, bool *done);
 
 }  // namespace lc

@@ -182,7 +182,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
 
   constexpr bool SWI = (EPI == LC_EPI_SWIGLU);
   Tile tile;
-  if (!find_tile<BM>(p, tile)) return;  // before any barrier
+  if (!find_tile<BM>(p, (int)blockIdx.x, (int)gridDim.x, tile)) return;  // before any barrier
   const int m0 = tile.m0, tn = tile.tn, m_lim = tile.m_lim, kbeg = tile.kbeg, kend = tile.kend;
   const bf16_t *const Bp = tile.B;
   void *const Cp = tile.C;
@@ -547,12 +547,12 @@ static lc_status check_gemm_args(const lc_gemm_args &a) {
 // so a grid of t tiles takes ceil(t / 256) rounds. Measured ns per k and round
 // (2048 x 2048 to 4096 x 11008 outputs, all compute units busy): 26 with 256 x
 // 256 tiles, 8.5 with 128 x 128, 4.4 with 64 x 64, about 2.2 with 32 x 32 (1.3 on a
-// half-full chip); a 256 x 256 round that fills// only part of the chip takes 17.7 + 8.3 x the part. The larger tile does more
-// work per round, the smaller ones fill the chip: 2048 x 2048 outputs (64, 256
-// or 1024 tiles) at K = 5632 take 107, 49 or 103 us; 2048 x 6144 at K = 2048
-// (192, 768 or 3072 tiles) 53, 60 or 135 us; 256 x 512 at K = 1408 (2, 8, 32 or 128
-// tiles) 31, 13, 9 or 6 us; 256 x 1536 at K = 512 with 64 or 32 (96 or 384 tiles)
-// 6.5 or 6.8. The choice depends on the output's size and the
+// half-full chip); a 256 x 256 round that fills only part of the chip takes 17.7 +
+// 8.3 x the part. The larger tile does more work per round, the smaller ones fill
+// the chip: 2048 x 2048 outputs (64, 256 or 1024 tiles) at K = 5632 take 107, 49 or
+// 103 us; 2048 x 6144 at K = 2048 (192, 768 or 3072 tiles) 53, 60 or 135 us; 256 x
+// 512 at K = 1408 (2, 8, 32 or 128 tiles) 31, 13, 9 or 6 us; 256 x 1536 at K = 512
+// with 64 or 32 (96 or 384 tiles) 6.5 or 6.8. The choice depends on the output's size and the
 // grouping only, so products of the same shape add in the same order whatever
 // their epilogue (an accumulated and a stored gradient are the same bits).
 static int pick_tile(const lc_gemm_args &a) {
@@ -575,17 +575,8 @@ static int pick_tile(const lc_gemm_args &a) {
   return c128 < c256 ? 128 : 256;
 }
 
-lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
-  LC_TRY(check_gemm_args(a));
-  if (a.dtype == LC_FP32 && a.group_mode != LC_GROUP_NONE)
-    return fail(LC_ERR_UNSUPPORTED, "gemm fp32: grouped products need bf16 operands");
-  if (a.dtype == LC_FP32) {
-    if (c_type(a) != LC_FP32 || (a.epilogue == LC_EPI_RESIDUAL && a.r_dtype != LC_FP32) ||
-        ((a.epilogue == LC_EPI_SWIGLU || a.epilogue == LC_EPI_SWIGLU_BWD) &&
-         a.aux_dtype != LC_FP32))
-      return fail(LC_ERR_UNSUPPORTED, "gemm fp32: every tensor must be fp32");
-    return gemm_f32_launch(a, s);
-  }
+// The bf16 kernels' own limits, and their launch parameters.
+static lc_status bf16_params(const lc_gemm_args &a, GemmP *out) {
   if (a.dtype != LC_BF16) return fail(LC_ERR_INVALID_ARG, "gemm: A/B dtype must be fp32 or bf16");
   // layout limits of the bf16 kernel: 16-byte rows along every contiguous extent
   if (a.N % 8) return fail(LC_ERR_UNSUPPORTED, "gemm bf16: N %% 8 != 0");
@@ -598,7 +589,8 @@ lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
   if (a.epilogue == LC_EPI_ROPE && (!aligned16(a.rope_cos) || !aligned16(a.rope_sin)))
     return fail(LC_ERR_INVALID_ARG, "gemm: RoPE tables must be 16-byte aligned");
 
-  GemmP p{};
+  GemmP &p = *out;
+  p = GemmP{};
   p.A = static_cast<const bf16_t *>(a.A);
   p.B = static_cast<const bf16_t *>(a.B);
   p.C = a.C;
@@ -642,7 +634,22 @@ lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
   p.c_dt = c_type(a);
   p.r_dt = a.r_dtype;
   p.aux_dt = a.aux_dtype;
+  return LC_OK;
+}
 
+lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
+  LC_TRY(check_gemm_args(a));
+  if (a.dtype == LC_FP32 && a.group_mode != LC_GROUP_NONE)
+    return fail(LC_ERR_UNSUPPORTED, "gemm fp32: grouped products need bf16 operands");
+  if (a.dtype == LC_FP32) {
+    if (c_type(a) != LC_FP32 || (a.epilogue == LC_EPI_RESIDUAL && a.r_dtype != LC_FP32) ||
+        ((a.epilogue == LC_EPI_SWIGLU || a.epilogue == LC_EPI_SWIGLU_BWD) &&
+         a.aux_dtype != LC_FP32))
+      return fail(LC_ERR_UNSUPPORTED, "gemm fp32: every tensor must be fp32");
+    return gemm_f32_launch(a, s);
+  }
+  GemmP p;
+  LC_TRY(bf16_params(a, &p));
   const int tile = pick_tile(a);
   if (tile != BM) return gemm_tile_launch(p, a, tile, s);
   const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
@@ -681,6 +688,37 @@ lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
   }
   return fail(LC_ERR_UNSUPPORTED, "gemm bf16: layout (a_kmajor=%d, b_kmajor=%d) not built for "
               "epilogue %d", (int)ak, (int)bk, a.epilogue);
+}
+
+// An input gradient x and a weight gradient w of one backward step that do not depend
+// on each other: one launch where both are products of 32 or 64 tiles (bf16) or
+// eight-wave 32 tiles (fp32), which leave most of the chip idle (small bf16 step 1012 ->
+// 955 us, tiny fp32 step 797 -> 648); larger tiles keep a launch each, as a 128 or 256
+// tile has another workgroup size. The results are those of the two launches.
+lc_status gemm_pair_launch(const lc_gemm_args &x, const lc_gemm_args &w, hipStream_t s) {
+  const bool form = x.dtype == w.dtype && x.group_mode == LC_GROUP_NONE && w.group_mode == LC_GROUP_NONE &&
+                    x.a_kmajor && !x.b_kmajor && !w.a_kmajor && !w.b_kmajor &&
+                    (x.epilogue == LC_EPI_STORE || x.epilogue == LC_EPI_SWIGLU_BWD) &&
+                    w.epilogue == LC_EPI_ACCUM_F32;
+  if (form) {
+    LC_TRY(check_gemm_args(x));
+    LC_TRY(check_gemm_args(w));
+    if (x.dtype == LC_FP32 && c_type(x) == LC_FP32 && (x.epilogue == LC_EPI_STORE || x.aux_dtype == LC_FP32)) {
+      bool done = false;
+      LC_TRY(gemm_f32_pair_launch(x, w, s, &done));
+      if (done) return LC_OK;
+    } else if (x.dtype == LC_BF16 && (x.epilogue == LC_EPI_STORE || (c_type(x) == LC_BF16 && x.aux_dtype == LC_FP32))) {
+      const int tx = pick_tile(x), tw = pick_tile(w);
+      if (tx <= 64 && tw <= 64) {
+        GemmP px, pw;
+        LC_TRY(bf16_params(x, &px));
+        LC_TRY(bf16_params(w, &pw));
+        return gemm_tile_pair_launch(px, x.epilogue, tx, pw, tw, s);
+      }
+    }
+  }
+  LC_TRY(gemm_launch(x, s));
+  return gemm_launch(w, s);
 }
 
 }  // namespace lc

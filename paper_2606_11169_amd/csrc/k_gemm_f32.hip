@@ -66,10 +66,12 @@ __device__ __forceinline__ int column(const F32P &p, int tn, int j, int *n, bool
   return *n;
 }
 
+typedef __attribute__((address_space(3))) float lds_f;
+
 // The waves' partial tiles added in wave order and the epilogue. `part`: W
 // tiles of T rows of T + 1 floats of LDS that no wave reads any more.
 template <int T, int W>
-__device__ __forceinline__ void finish(const F32P &p, float *part, const f32x16_v (&acc)[T / 32][T / 32], int m0,
+__device__ __forceinline__ void finish(const F32P &p, lds_f *part, const f32x16_v (&acc)[T / 32][T / 32], int m0,
                                        int tn, int w, int lane) {
   constexpr int F = T / 32, LD = T + 1;
   const int l32 = lane & 31, h = lane >> 5;
@@ -168,7 +170,6 @@ struct Slice {
 #pragma unroll
       for (int u = 0; u < 4; ++u) x[u] = v[u];
     } else {
-      typedef __attribute__((address_space(3))) float lds_f;
       const lds_f *s = reinterpret_cast<const lds_f *>(t) + k * T + r;
 #pragma unroll
       for (int u = 0; u < 4; ++u) x[u] = s[u * T];
@@ -181,17 +182,19 @@ constexpr int NST = 4;  // stages of the ring
 // SUB slices per stage; each of the W waves multiplies 8 G k of every stage. Eight
 // waves halve a tile's chain of products (two waves per SIMD instead of one; tiny step
 // 850 -> 797 us).
+template <int T, int W> constexpr int ring_lds() {
+  constexpr int part = W * T * (T + 1) * 4, ring = NST * 2 * (64 / T * (W / 4)) * Slice<T, true>::BYTES;
+  return ring > part ? ring : part;
+}
 template <int T, int W, bool A_K, bool B_K>
-__global__ __launch_bounds__(64 * W) void gemm_f32_ring_kernel(F32P p) {
+__device__ __forceinline__ void ring_block(F32P p, unsigned wg, lds_t *R0) {
   constexpr int F = T / 32, SUB = 64 / T * (W / 4), KS = 32 * SUB, G = 64 / T;
   constexpr int OPB = Slice<T, true>::BYTES, STAGE = 2 * SUB * OPB;
   constexpr int LPW = 2 * SUB * (T / 8) / W;  // loads per wave and stage: A by the first half of the waves
-  constexpr int PART = W * T * (T + 1) * 4;
   static_assert(KS == W * 8 * G && LPW == 4, "");
-  __shared__ __align__(16) char ring[NST * STAGE > PART ? NST * STAGE : PART];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m0 = (int)(blockIdx.x / p.tiles_n) * T, tn = (int)(blockIdx.x % p.tiles_n);
+  const int m0 = (int)(wg / p.tiles_n) * T, tn = (int)(wg % p.tiles_n);
   const int grp = w / (W / 2), wo = w % (W / 2);
   const i32x4_v rs = grp == 0 ? make_rsrc(p.A, p.a_bytes) : make_rsrc(p.B, p.b_bytes);
   const bool gk = grp == 0 ? A_K : B_K;
@@ -216,7 +219,6 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_ring_kernel(F32P p) {
     vo[t] = ok ? (uint32_t)((gk ? (int64_t)row * ld + kl[t] : (int64_t)kl[t] * ld + row) * 4) : OOB;
   }
   const uint32_t kbw = gk ? 4u : (uint32_t)(ld * 4);
-  lds_t *const R0 = LDS_AS(char, ring);
   lds_t *const dst0 = R0 + (2 * sub + grp) * OPB + q0 * 1024;
   const int ns = (p.K + KS - 1) / KS;
   auto load = [&](int st) {
@@ -284,7 +286,23 @@ __global__ __launch_bounds__(64 * W) void gemm_f32_ring_kernel(F32P p) {
     if (st + 1 < ns) step(st + 1, fa[1], fb[1], fa[0], fb[0]);
   }
   __syncthreads();  // every wave's last fragment reads are done
-  finish<T, W>(p, reinterpret_cast<float *>(ring), acc, m0, tn, w, lane);
+  finish<T, W>(p, reinterpret_cast<lds_f *>(R0), acc, m0, tn, w, lane);
+}
+
+template <int T, int W, bool A_K, bool B_K>
+__global__ __launch_bounds__(64 * W) void gemm_f32_ring_kernel(F32P p) {
+  __shared__ __align__(16) char ring[ring_lds<T, W>()];
+  ring_block<T, W, A_K, B_K>(p, blockIdx.x, LDS_AS(char, ring));
+}
+
+// An input gradient's nx tiles and a weight gradient's in one grid: the same bits as
+// a launch for each. A tiny step (d 128, 128 tokens, 2 layers, 4 microbatches; 32
+// launches fewer) 797 -> 648 us.
+__global__ __launch_bounds__(512) void gemm_f32_pair_kernel(F32P x, F32P w, int nx) {
+  __shared__ __align__(16) char ring[ring_lds<32, 8>()];
+  const unsigned i = blockIdx.x, n = (unsigned)nx;
+  if (i < n) ring_block<32, 8, true, false>(x, i, LDS_AS(char, ring));
+  else ring_block<32, 8, false, false>(w, i - n, LDS_AS(char, ring));
 }
 
 // ------------------------------------------------------------------ registers
@@ -375,7 +393,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(F32P p) {
     if (k + 2 * STEP < p.K) load(k + 2 * STEP, a[0], b[0]);
     multiply(a[1], b[1]);
   }
-  finish<T, NW>(p, part, acc, m0, tn, w, lane);
+  finish<T, NW>(p, LDS_AS(float, part), acc, m0, tn, w, lane);
 }
 
 template <int T>
@@ -408,10 +426,17 @@ lc_status run_f32(F32P p, bool ak, bool bk, bool ring, hipStream_t s) {
 
 }  // namespace
 
-lc_status gemm_f32_launch(const lc_gemm_args &a, hipStream_t s) {
-  if (a.epilogue == LC_EPI_SWIGLU && !a.b_kmajor)
-    return fail(LC_ERR_UNSUPPORTED, "gemm fp32: SwiGLU needs k-major B");
-  F32P p{};
+namespace {
+
+struct Plan {
+  F32P p;
+  bool ring;
+  int64_t tiles32, tiles64;
+};
+
+Plan plan_of(const lc_gemm_args &a) {
+  Plan r{};
+  F32P &p = r.p;
   p.A = static_cast<const float *>(a.A);
   p.B = static_cast<const float *>(a.B);
   p.C = static_cast<float *>(a.C);
@@ -434,22 +459,46 @@ lc_status gemm_f32_launch(const lc_gemm_args &a, hipStream_t s) {
   p.hd = a.head_dim;
   p.vec_a = a.lda % 4 == 0;
   p.vec_b = a.ldb % 4 == 0;
-  // 64 x 64 tiles read half the operand bytes per product; 32 x 32 tiles where
-  // those would leave a quarter of the compute units or more without one
   const int64_t n = a.epilogue == LC_EPI_SWIGLU ? 2 * a.N : a.N;
-  const int64_t tiles64 = ((a.M + 63) / 64) * ((n + 63) / 64);
+  r.tiles64 = ((a.M + 63) / 64) * ((n + 63) / 64);
+  r.tiles32 = ((a.M + 31) / 32) * ((n + 31) / 32);
   const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
   // The ring's loads are 16 bytes: rows of whole 16-byte runs of which none is part
   // inside the operand (a part past K would not be zero), 32-bit offsets
   const int64_t brows = a.epilogue == LC_EPI_SWIGLU ? 2 * a.N : a.N;
   const int64_t ae = 4 * (ak ? (a.M - 1) * a.lda + a.K : (a.K - 1) * a.lda + a.M);
   const int64_t be = 4 * (bk ? (brows - 1) * a.ldb + a.K : (a.K - 1) * a.ldb + brows);
-  const bool ring = p.vec_a && p.vec_b && (!(ak || bk) || a.K % 4 == 0) && (ak || a.M % 4 == 0) &&
-                    (bk || (a.N % 4 == 0 && a.epilogue != LC_EPI_ROPE)) &&
-                    ae < (int64_t)OOB && be < (int64_t)OOB;
+  r.ring = p.vec_a && p.vec_b && (!(ak || bk) || a.K % 4 == 0) && (ak || a.M % 4 == 0) &&
+           (bk || (a.N % 4 == 0 && a.epilogue != LC_EPI_ROPE)) &&
+           ae < (int64_t)OOB && be < (int64_t)OOB;
   p.a_bytes = (uint32_t)ae;
   p.b_bytes = (uint32_t)be;
-  return tiles64 >= 192 ? run_f32<64>(p, ak, bk, ring, s) : run_f32<32>(p, ak, bk, ring, s);
+  return r;
+}
+
+}  // namespace
+
+lc_status gemm_f32_launch(const lc_gemm_args &a, hipStream_t s) {
+  if (a.epilogue == LC_EPI_SWIGLU && !a.b_kmajor)
+    return fail(LC_ERR_UNSUPPORTED, "gemm fp32: SwiGLU needs k-major B");
+  const Plan r = plan_of(a);
+  const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
+  // 64 x 64 tiles read half the operand bytes per product; 32 x 32 tiles where
+  // those would leave a quarter of the compute units or more without one
+  return r.tiles64 >= 192 ? run_f32<64>(r.p, ak, bk, r.ring, s) : run_f32<32>(r.p, ak, bk, r.ring, s);
+}
+
+lc_status gemm_f32_pair_launch(const lc_gemm_args &x, const lc_gemm_args &w, hipStream_t s, bool *done) {
+  Plan a = plan_of(x), b = plan_of(w);
+  *done = false;
+  if (!a.ring || !b.ring || a.tiles64 >= 192 || b.tiles64 >= 192 || a.tiles32 > 256 || b.tiles32 > 256)
+    return LC_OK;
+  a.p.tiles_n = (unsigned)((x.N + 31) / 32);
+  b.p.tiles_n = (unsigned)((w.N + 31) / 32);
+  hipLaunchKernelGGL(gemm_f32_pair_kernel, dim3((unsigned)(a.tiles32 + b.tiles32)), dim3(512), 0, s, a.p, b.p,
+                     (int)a.tiles32);
+  *done = true;
+  return check_launch("gemm_f32_pair_kernel");
 }
 
 }  // namespace lc

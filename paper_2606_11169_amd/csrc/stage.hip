@@ -106,6 +106,18 @@ lc_status wgrad_launch(lc_stage *st, const lc_gemm_args &a, hipStream_t s) {
   return LC_OK;
 }
 
+// An input gradient product and the weight gradient product that goes with it
+// (independent of each other); w NULL: the input gradient alone. Timed weight
+// products keep a launch of their own.
+lc_status grad_launch(lc_stage *st, const lc_gemm_args &x, const lc_gemm_args *w, hipStream_t s) {
+  if (!w) return gemm_launch(x, s);
+  if (st->tn < (int32_t)st->tflop.size()) {
+    LC_TRY(gemm_launch(x, s));
+    return wgrad_launch(st, *w, s);
+  }
+  return gemm_pair_launch(x, *w, s);
+}
+
 lc_norm_args norm_base(int64_t T, int64_t d, float eps) {
   lc_norm_args a;
   memset(&a, 0, sizeof a);
@@ -446,7 +458,7 @@ static lc_status backward_layers(lc_stage *st, const lc_param_bufs *pb, const vo
     void *dh = (split && !copies) ? WL.at(P.w_dh) : ws + P.s_dh;
     void *dh_op = !copies ? dh : split ? WL.at(P.w_dh) : ws + P.s_dh16;
     char *dqkv = split ? static_cast<char *>(WL.at(P.w_dqkv)) : ws + P.s_dqkv;
-    lc_gemm_args a;
+    lc_gemm_args a, g;  // input and weight gradient
     if (d.n_experts > 0) {
       LC_TRY(moe_backward(st, w, L, dy_res, dy_dt, s, split ? &WL : nullptr));
     } else {
@@ -456,29 +468,27 @@ static lc_status backward_layers(lc_stage *st, const lc_param_bufs *pb, const vo
     a.B = w.wp(pp.w2); a.ldb = F; a.b_kmajor = 0;
     a.C = da; a.ldc = 2 * F; a.c_dtype = ty.op;
     a.aux0 = L.at(P.gate); a.aux1 = L.at(P.up); a.ld_aux = F; a.aux_dtype = ty.res;
-    LC_TRY(gemm_launch(a, s));
     // G[W2] += dy^T act
     if (!split) {
-      a = gemm_base(dt, gepi, D, F, T);
-      a.A = dy_op; a.lda = D; a.a_kmajor = 0;
-      a.B = L.at(P.act); a.ldb = F; a.b_kmajor = 0;
-      a.C = w.gp(pp.w2); a.ldc = F;
-      LC_TRY(wgrad_launch(st, a, s));
+      g = gemm_base(dt, gepi, D, F, T);
+      g.A = dy_op; g.lda = D; g.a_kmajor = 0;
+      g.B = L.at(P.act); g.ldb = F; g.b_kmajor = 0;
+      g.C = w.gp(pp.w2); g.ldc = F;
     }
+    LC_TRY(grad_launch(st, a, split ? nullptr : &g, s));
     // dn2 = [dgate | dup] [W1; W3]
     a = gemm_base(dt, LC_EPI_STORE, T, D, 2 * F);
     a.A = da; a.lda = 2 * F; a.a_kmajor = 1;
     a.B = w.wp(pp.w1); a.ldb = D; a.b_kmajor = 0;
     a.C = dn; a.ldc = D; a.c_dtype = ty.res;
-    LC_TRY(gemm_launch(a, s));
     // G[W1; W3] += [dgate | dup]^T n2
     if (!split) {
-      a = gemm_base(dt, gepi, 2 * F, D, T);
-      a.A = da; a.lda = 2 * F; a.a_kmajor = 0;
-      a.B = L.at(P.n2); a.ldb = D; a.b_kmajor = 0;
-      a.C = w.gp(pp.w1); a.ldc = D;
-      LC_TRY(wgrad_launch(st, a, s));
+      g = gemm_base(dt, gepi, 2 * F, D, T);
+      g.A = da; g.lda = 2 * F; g.a_kmajor = 0;
+      g.B = L.at(P.n2); g.ldb = D; g.b_kmajor = 0;
+      g.C = w.gp(pp.w1); g.ldc = D;
     }
+    LC_TRY(grad_launch(st, a, split ? nullptr : &g, s));
     }
     // dh = dy + RMSNorm2'(dn2); G[g2] += ... (or its partial sums)
     lc_norm_args nb = norm_base(T, D, d.rms_eps);
@@ -501,15 +511,14 @@ static lc_status backward_layers(lc_stage *st, const lc_param_bufs *pb, const vo
     a.A = dh_op; a.lda = D; a.a_kmajor = 1;
     a.B = w.wp(pp.wo); a.ldb = D; a.b_kmajor = 0;
     a.C = dO; a.ldc = D; a.c_dtype = ty.op;
-    LC_TRY(gemm_launch(a, s));
     // G[Wo] += dh^T o
     if (!split) {
-      a = gemm_base(dt, gepi, D, D, T);
-      a.A = dh_op; a.lda = D; a.a_kmajor = 0;
-      a.B = L.at(P.o); a.ldb = D; a.b_kmajor = 0;
-      a.C = w.gp(pp.wo); a.ldc = D;
-      LC_TRY(wgrad_launch(st, a, s));
+      g = gemm_base(dt, gepi, D, D, T);
+      g.A = dh_op; g.lda = D; g.a_kmajor = 0;
+      g.B = L.at(P.o); g.ldb = D; g.b_kmajor = 0;
+      g.C = w.gp(pp.wo); g.ldc = D;
     }
+    LC_TRY(grad_launch(st, a, split ? nullptr : &g, s));
     // dq, dk, dv (dq, dk rotated back)
     char *qkv = static_cast<char *>(L.at(P.qkv));
     lc_attn_args at;
@@ -546,15 +555,14 @@ static lc_status backward_layers(lc_stage *st, const lc_param_bufs *pb, const vo
     a.A = dqkv; a.lda = QC; a.a_kmajor = 1;
     a.B = w.wp(pp.wq); a.ldb = D; a.b_kmajor = 0;
     a.C = dn; a.ldc = D; a.c_dtype = ty.res;
-    LC_TRY(gemm_launch(a, s));
     // G[Wq;Wk;Wv] += [dq|dk|dv]^T n1
     if (!split) {
-      a = gemm_base(dt, gepi, QC, D, T);
-      a.A = dqkv; a.lda = QC; a.a_kmajor = 0;
-      a.B = L.at(P.n1); a.ldb = D; a.b_kmajor = 0;
-      a.C = w.gp(pp.wq); a.ldc = D;
-      LC_TRY(wgrad_launch(st, a, s));
+      g = gemm_base(dt, gepi, QC, D, T);
+      g.A = dqkv; g.lda = QC; g.a_kmajor = 0;
+      g.B = L.at(P.n1); g.ldb = D; g.b_kmajor = 0;
+      g.C = w.gp(pp.wq); g.ldc = D;
     }
+    LC_TRY(grad_launch(st, a, split ? nullptr : &g, s));
     // dx = dh + RMSNorm1'(dn1); G[g1] += ... (or its partial sums)
     nb.dn = dn; nb.dn_dtype = ty.res;
     nb.x = xin; nb.x_dtype = x_dt;
