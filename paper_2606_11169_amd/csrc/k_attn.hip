@@ -263,7 +263,7 @@ __device__ __forceinline__ void query_block_of(const AttnP &p, int i, int nqb, i
 // KG = 1: 8 waves x 32 queries. KG = 2: 4 x 32 queries, the key blocks dealt in
 // turn to two groups of four waves, each with its own ring, running maximum, sum
 // and output, merged at the end through LDS (group 0's first). A grid of 256-query
-// blocks smaller than two per compute unit lasts as long as its longest causal
+// blocks that is small (see small_grid) lasts as long as its longest causal
 // block; halving the queries and the chain of each workgroup fills the chip and
 // evens it out, for twice the K and V traffic (16 heads of 2048: 59 -> 40 us; at 32
 // heads of 4096, 512 blocks, both split evenly already and the traffic costs 5%).
@@ -500,7 +500,7 @@ __device__ __forceinline__ void store_row_t(__bf16 *row, const f32x16_v (&acc)[4
 // dQ: one workgroup per 256 queries; LDS stage = K (QE) | V (bf16), plus the
 // bf16 rows of K for fp16 inputs. Each query's D = dO.O is formed here from
 // the dO row the lane pair holds and written out for the dK/dV kernel.
-// KG = 2 (grids smaller than two workgroups per compute unit, as in the forward):
+// KG = 2 (small grids, as in the forward):
 // 128 queries, waves w and w + 4 own the same 32 and take the two halves of every
 // key block; their sums are added through LDS (16 heads of 2048: 95 -> 69 us).
 template <typename QE> constexpr int dq_smem() { return 2 * (std::is_same<QE, __bf16>::value ? 2 : 3) * TILE; }
@@ -1101,16 +1101,29 @@ lc_status check_extents(const lc_attn_args &a) {
   return LC_OK;
 }
 
-// Fewer than two 256-query workgroups per compute unit (forward, dQ): the KG = 2
-// kernels' smaller workgroups. From two on, the heavy blocks first and the light
-// ones after them fill the chip evenly.
-bool small_grid(unsigned blocks) { return blocks < 512; }
+// The KG = 2 kernels (128 queries per workgroup) for the forward and dQ: where their
+// blocks have a compute unit each, which halves the longest chain (S = 256, 104 heads:
+// forward 14.8 -> 11.4 us, S = 4096, 8 heads: 96 -> 57), or where the longest causal
+// chain of 256-query blocks (nb key blocks) is well over a compute unit's mean share of
+// them, bh nb (nb + 1) / 2 / 256: the ratio is 512 / (bh (nb + 1)). KG = 2 over KG = 1 at
+// that ratio, forward | whole backward: nb = 3 (S = 640) 0.90 | 0.98 (2.5), 1.08 | 1.02
+// (2.0); nb = 4 (S = 1024) 0.84 | 0.95 (2.4), 1.0-1.10 | 1.01 (1.8); nb = 5 (S = 1280) 0.83 |
+// 0.93 (2.4), 0.89 | 0.97 (1.8), 1.02-1.04 | 1.0 (1.67); nb = 8 (S = 2048) 0.80 | 0.94 (1.8),
+// 1.06 | 1.07 (1.4). Below, both grids are even and the second pass over K and V is
+// lost; with up to four blocks of a chain it shows earlier; two blocks (S = 512, 80 heads,
+// ratio 2.1: backward 71 -> 73 us) never gain it back. How the blocks fall on the
+// compute units adds some per cent either way (S = 1664, fp16, 31 heads: forward 44 us
+// -> 41 to 47, backward 132 -> 124; 26 heads 43 -> 32).
+bool small_grid(int S, unsigned bh) {
+  const unsigned n = (unsigned)(S / KV_ROWS) * bh, nb = (unsigned)((S + ROWS - 1) / ROWS);
+  return n <= 256 || (n <= 512 && nb >= 3 && bh * (nb + 1) <= (nb <= 4 ? 220u : 300u));
+}
 
 template <typename QE>
 lc_status fwd_mc(const lc_attn_args &a, hipStream_t s) {
   LC_TRY(check_extents(a));
   const unsigned bh = (unsigned)(a.H * a.B), nb = (unsigned)((a.S + ROWS - 1) / ROWS);
-  if (small_grid(nb * bh))
+  if (small_grid(a.S, bh))
     hipLaunchKernelGGL((attn_fwd_kernel<QE, 2>), dim3((unsigned)(a.S / QB) * bh), dim3(NT), 0, s, mc_params(a));
   else
     hipLaunchKernelGGL((attn_fwd_kernel<QE, 1>), dim3(nb * bh), dim3(NT), 0, s, mc_params(a));
@@ -1136,7 +1149,7 @@ lc_status bwd_mc(const lc_attn_args &a, hipStream_t s) {
     LC_TRY(check_launch("attn_bwd_both_kernel"));
   } else {
     // dQ first: it writes D, which the dK/dV kernel reads
-    if (small_grid(nb * bh))
+    if (small_grid(a.S, bh))
       hipLaunchKernelGGL((attn_bwd_dq_kernel<QE, 2>), dim3(n), dim3(NT), 0, s, p);
     else
       hipLaunchKernelGGL((attn_bwd_dq_kernel<QE, 1>), dim3(nb * bh), dim3(NT), 0, s, p);

@@ -1,5 +1,5 @@
 """The attention kernels' workgroup shapes (256 queries; 128 queries with the
-keys split over two wave groups, for grids under 512 blocks; dQ and dK/dV in one grid
+keys split over two wave groups, for small grids; dQ and dK/dV in one grid
 up to 256 blocks of each) at sequence lengths
 whose last block is half full and whose first block leaves the second group
 without a visible key: against float64 of the same fp16/bf16 q, k, v."""
