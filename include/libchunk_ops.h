@@ -187,6 +187,9 @@ lc_status lc_rmsnorm_backward_noalloc(const lc_norm_args *args, void *stream);
  * rounded to bf16 (from the fp16 values, or from the fp32 values those were
  * rounded from); the backward then reads them instead of writing its own
  * (NULL: it writes them into the scratch).
+ * Overlap: o may lie over q, dq over o, and dk, dv over k, v, element for
+ * element (the same strides); no other output may overlap a tensor that the
+ * call reads.
  * Types: matrix-core path: q, k, v LC_FP16 or LC_BF16 (`dtype`; forward
  * products in that type), o, dout, dq, dk, dv LC_BF16 (gradient products in
  * bf16), head_dim 128, S a multiple of 128. fp32 path: everything LC_FP32,

@@ -1130,6 +1130,22 @@ lc_status fwd_mc(const lc_attn_args &a, hipStream_t s) {
   return check_launch("attn_fwd_kernel");
 }
 
+// Whether dk or dv lies over the k, v rows that dQ reads (a caller may keep no other
+// buffer for them). Sequential dQ and dK/dV launches allow it: dQ is done with k and v,
+// and a dK/dV workgroup reads only the keys that it writes. In one grid it is a race.
+bool grads_over_keys(const AttnP &p) {
+  const int64_t rows = (int64_t)p.B * p.S, w = (int64_t)p.Hkv * HD;
+  auto over = [&](const void *x, int64_t ldx, const void *y, int64_t ldy) {
+    const char *a = static_cast<const char *>(x), *b = static_cast<const char *>(y);
+    return a < b + ((rows - 1) * ldy + w) * 2 && b < a + ((rows - 1) * ldx + w) * 2;
+  };
+  auto hit = [&](const void *g) {
+    return over(g, p.ld_d, p.k, p.ld_qkv) || over(g, p.ld_d, p.v, p.ld_qkv) ||
+           over(g, p.ld_d, p.kb, p.ld_kb) || over(g, p.ld_d, p.vb, p.ld_vb);
+  };
+  return p.G == 1 && (hit(p.dk) || hit(p.dv));  // (G > 1: written after both, from the shares)
+}
+
 template <typename QE>
 lc_status bwd_mc(const lc_attn_args &a, hipStream_t s) {
   LC_TRY(check_extents(a));
@@ -1141,7 +1157,7 @@ lc_status bwd_mc(const lc_attn_args &a, hipStream_t s) {
   }
   const unsigned bh = (unsigned)(a.H * a.B), nb = (unsigned)((a.S + ROWS - 1) / ROWS);
   const unsigned n = (unsigned)(a.S / KV_ROWS) * bh;  // blocks of 128 keys, and of 128 queries
-  if (n <= 256) {
+  if (n <= 256 && !grads_over_keys(p)) {
     const int64_t rows = (int64_t)a.B * a.S * a.H;
     hipLaunchKernelGGL(attn_bwd_d_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s, p);
     LC_TRY(check_launch("attn_bwd_d_kernel"));

@@ -61,3 +61,36 @@ def test_both_shapes(B, S, H, kv, dt):
     assert rel(o.view_as(ro), ro) < 2 ** -8
     assert rel(lse, rl) < 1e-5
     assert rel(dqkv.view_as(rg), rg) < 2 ** -6.5
+
+
+@pytest.mark.parametrize("dt", ["fp16", "bf16"])
+@pytest.mark.parametrize("B,S,H,kv", [(1, 1024, 4, 4), (1, 2048, 16, 16), (1, 1024, 4, 2)])
+def test_key_gradients_in_place(B, S, H, kv, dt):
+    """dk, dv over k, v give what separate buffers give (sizes at which dQ and dK/dV
+    otherwise share a grid). The sums that form D and dQ may then be added in another
+    order: a few fp32 roundings before the one to bf16, so at most a small share of the
+    values one bf16 step (2^-8) apart."""
+    banner(f"attention key gradients in place B={B} S={S} H={H}/{kv} {dt}")
+    tdt, ldt = (torch.float16, lc.LC_FP16) if dt == "fp16" else (torch.bfloat16, lc.LC_BF16)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S + H)
+    T, d, dkv = B * S, H * 128, kv * 128
+    q = torch.randn((T, d), generator=g, device=DEV).to(tdt)
+    k, v = (torch.randn((T, d), generator=g, device=DEV).to(tdt) for _ in range(2))  # rows of d: one stride
+    dout = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16)
+    o, lse = torch.empty_like(dout), torch.empty((B, H, S), device=DEV)
+    lc.lc_attention_forward(ldt, lc.LC_BF16, B, S, H, 128, q, k, v, d, o, d, lse, Hkv=kv)
+    nb = lc.lc_attention_scratch_bytes(B, S, H, kv)
+    scratch = torch.empty(nb, dtype=torch.uint8, device=DEV)
+
+    def backward(dk, dv):
+        dq = torch.empty_like(dout)
+        lc.lc_attention_backward(ldt, lc.LC_BF16, B, S, H, 128, q, k, v, d, o, dout, d, lse, dq, dk, dv, d,
+                                 None, None, scratch, nb, Hkv=kv)
+        return [t.view(torch.bfloat16)[:, :w].clone() for t, w in ((dq, d), (dk, dkv), (dv, dkv))]
+
+    want = backward(torch.empty_like(dout), torch.empty_like(dout))
+    got = backward(k, v)
+    for a, b in zip(got, want):
+        assert bool(torch.isfinite(b).all())
+        assert rel(a, b.double()) < 2 ** -10
