@@ -130,6 +130,14 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 inline unsigned ceil_div(size_t a, size_t b) { return unsigned((a + b - 1) / b); }
 
+// A grid of at least n workgroups (of at most 512 threads) numbered blockIdx.x +
+// blockIdx.y * gridDim.x: a second dimension where one would pass the launch limit of
+// 2^32 work-items; the kernel leaves numbers at or past n.
+inline dim3 grid_2d(int64_t n) {
+  constexpr int64_t X = (int64_t)1 << 22;
+  return n <= X ? dim3((unsigned)n) : dim3((unsigned)X, (unsigned)((n + X - 1) / X));
+}
+
 // ------------------------------------------------------------------ internal launchers
 // Defined in the kernel translation units; used by the stage composer.
 lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s);

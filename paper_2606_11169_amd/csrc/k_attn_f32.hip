@@ -176,12 +176,16 @@ struct Merge {
 };
 
 // Block, head and batch row of a workgroup: the heaviest blocks (most queries
-// or keys to visit) first, heads fastest
-__device__ __forceinline__ void place(int nblk, int heads, int batch, bool last_first, int &blk, int &h, int &b) {
-  const int nbh = heads * batch, i = (int)blockIdx.x;
-  blk = last_first ? nblk - 1 - i / nbh : i / nbh;
-  h = (i % nbh) % heads;
-  b = (i % nbh) / heads;
+// or keys to visit) first, heads fastest. False when it has none (a grid of two
+// dimensions is an upper bound; uniform across the workgroup).
+__device__ __forceinline__ bool place(int nblk, int heads, int batch, bool last_first, int &blk, int &h, int &b) {
+  const int64_t nbh = (int64_t)heads * batch, i = blockIdx.x + (int64_t)blockIdx.y * gridDim.x;
+  if (i >= nbh * nblk) return false;
+  const int at = (int)(i / nbh);
+  blk = last_first ? nblk - 1 - at : at;
+  h = (int)((i % nbh) % heads);
+  b = (int)((i % nbh) / heads);
+  return true;
 }
 
 template <int NI>
@@ -190,7 +194,7 @@ __global__ __launch_bounds__(NTF) void attn_f32_fwd_kernel(AttnF p) {
   __shared__ float sm[NW][QR], sl[NW][QR], sf[NW + 1][QR];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   int qb, h, b;
-  place((p.S + QR - 1) / QR, p.H, p.B, true, qb, h, b);
+  if (!place((p.S + QR - 1) / QR, p.H, p.B, true, qb, h, b)) return;  // before any barrier
   const int64_t r0 = (int64_t)b * p.S;
   const int q0 = qb * QR, qi = q0 + c, kvh = h / p.G;
   const float *K = p.k + r0 * p.ld_qkv + (int64_t)kvh * p.hd, *V = p.v + r0 * p.ld_qkv + (int64_t)kvh * p.hd;
@@ -293,7 +297,7 @@ __global__ __launch_bounds__(NTF) void attn_f32_dq_kernel(AttnF p) {
   __shared__ __align__(16) float sq[Merge<NI>::FLOATS];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   int qb, h, b;
-  place((p.S + QR - 1) / QR, p.H, p.B, true, qb, h, b);
+  if (!place((p.S + QR - 1) / QR, p.H, p.B, true, qb, h, b)) return;  // before any barrier
   const int64_t r0 = (int64_t)b * p.S;
   const int q0 = qb * QR, qi = q0 + c, qc = min(qi, p.S - 1), kvh = h / p.G;
   const float *K = p.k + r0 * p.ld_qkv + (int64_t)kvh * p.hd, *V = p.v + r0 * p.ld_qkv + (int64_t)kvh * p.hd;
@@ -345,7 +349,7 @@ __global__ __launch_bounds__(NTF) void attn_f32_dkdv_kernel(AttnF p) {
   __shared__ __align__(16) float sk[Merge<NI>::FLOATS], sv[Merge<NI>::FLOATS];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   int kb, kvh, b;
-  place((p.S + QR - 1) / QR, p.Hkv, p.B, false, kb, kvh, b);
+  if (!place((p.S + QR - 1) / QR, p.Hkv, p.B, false, kb, kvh, b)) return;  // before any barrier
   const int64_t r0 = (int64_t)b * p.S;
   const int k0 = kb * QR, kj = k0 + c;
   const int64_t kr = (r0 + min(kj, p.S - 1)) * p.ld_qkv + (int64_t)kvh * p.hd;
@@ -432,19 +436,13 @@ void with_blocks(int hd, F f) {
 }
 
 // one workgroup per block of 16 rows, head and batch row
-lc_status grid_of(const AttnF &p, int heads, dim3 *g) {
-  const int64_t n = (int64_t)((p.S + QR - 1) / QR) * heads * p.B;
-  if (n > INT32_MAX / NTF) return fail(LC_ERR_UNSUPPORTED, "attention fp32: too many rows for one launch");
-  *g = dim3((unsigned)n);
-  return LC_OK;
-}
+dim3 grid_of(const AttnF &p, int heads) { return grid_2d((int64_t)((p.S + QR - 1) / QR) * heads * p.B); }
 
 }  // namespace
 
 lc_status attn_f32_fwd_launch(const lc_attn_args &a, hipStream_t s) {
   const AttnF p = f32_params(a);
-  dim3 grid;
-  LC_TRY(grid_of(p, p.H, &grid));
+  const dim3 grid = grid_of(p, p.H);
   with_blocks(p.hd, [&](auto ni) {
     hipLaunchKernelGGL(attn_f32_fwd_kernel<decltype(ni)::value>, grid, dim3(NTF), 0, s, p);
   });
@@ -453,9 +451,7 @@ lc_status attn_f32_fwd_launch(const lc_attn_args &a, hipStream_t s) {
 
 lc_status attn_f32_bwd_launch(const lc_attn_args &a, hipStream_t s) {
   const AttnF p = f32_params(a);
-  dim3 gq, gk;
-  LC_TRY(grid_of(p, p.H, &gq));
-  LC_TRY(grid_of(p, p.Hkv, &gk));
+  const dim3 gq = grid_of(p, p.H), gk = grid_of(p, p.Hkv);
   with_blocks(p.hd, [&](auto ni) {
     hipLaunchKernelGGL(attn_f32_dq_kernel<decltype(ni)::value>, gq, dim3(NTF), 0, s, p);
   });

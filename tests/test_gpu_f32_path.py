@@ -164,3 +164,31 @@ def test_values_not_finite_reach_only_who_sees_them(bad):
     close(d[at + 1:, hd:], d0[at + 1:, hd:].double(), 1e-6)  # keys that query 40 does not see
     assert not bool(torch.isfinite(d[:at + 1, 2 * hd + 3]).any())
     close(d[:at, :hd], d0[:at, :hd].double(), 1e-6)          # dq of other queries
+
+
+def test_attention_more_blocks_than_one_grid_dimension():
+    """2^23 + 5 sequences of 9 tokens, a block of 16 rows each: a grid of two
+    dimensions (one holds fewer than 2^32 work-items, 256 per block). The first, the middle and the last ones
+    against float64."""
+    B, S, hd = (1 << 23) + 5, 9, 2
+    banner(f"attention f32 of {B} sequences")
+    g = gen(9)
+    q, k, v, dout = (torch.randn((B * S, hd), generator=g, device=DEV) for _ in range(4))
+    o, lse = torch.empty_like(q), torch.empty((B, 1, S), device=DEV)
+    lc.lc_attention_forward(F32, F32, B, S, 1, hd, q, k, v, hd, o, hd, lse)
+    dq, dk, dv = (torch.empty_like(q) for _ in range(3))
+    nb = lc.lc_attention_scratch_bytes(B, S, 1)
+    scratch = torch.empty(nb, dtype=torch.uint8, device=DEV)
+    lc.lc_attention_backward(F32, F32, B, S, 1, hd, q, k, v, hd, o, dout, hd, lse, dq, dk, dv, hd, None, None,
+                             scratch, nb)
+    at = torch.cat([torch.arange(0, 1000), torch.arange((1 << 22) - 500, (1 << 22) + 500),
+                    torch.arange(B - 1000, B)]).to(DEV)
+    x = [t.view(B, S, hd)[at].double().requires_grad_() for t in (q, k, v)]
+    sc = (x[0].unsqueeze(2) * x[1].unsqueeze(1)).sum(-1) / math.sqrt(hd)
+    sc = sc.masked_fill(torch.ones((S, S), dtype=torch.bool, device=DEV).triu(1), -math.inf)
+    oh = (torch.softmax(sc, -1).unsqueeze(-1) * x[2].unsqueeze(1)).sum(2)
+    oh.backward(dout.view(B, S, hd)[at].double())
+    close(o.view(B, S, hd)[at], oh.detach(), 3e-6)
+    close(lse[at, 0], torch.logsumexp(sc, -1).detach(), 3e-6)
+    for a, b in zip((dq, dk, dv), x):
+        close(a.view(B, S, hd)[at], b.grad, 3e-6)
