@@ -130,12 +130,17 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 inline unsigned ceil_div(size_t a, size_t b) { return unsigned((a + b - 1) / b); }
 
-// A grid of at least n workgroups (of at most 512 threads) numbered blockIdx.x +
-// blockIdx.y * gridDim.x: a second dimension where one would pass the launch limit of
-// 2^32 work-items; the kernel leaves numbers at or past n.
-inline dim3 grid_2d(int64_t n) {
-  constexpr int64_t X = (int64_t)1 << 22;
-  return n <= X ? dim3((unsigned)n) : dim3((unsigned)X, (unsigned)((n + X - 1) / X));
+// launch(first, count) for n workgroups in parts that keep under the launch limit of 2^32
+// work-items (for workgroups of at most 512 threads); the kernel adds `first` to its index
+template <typename F>
+inline void launch_parts(uint32_t n, F launch) {
+  constexpr uint32_t PART = 1u << 22;
+  for (uint32_t first = 0; n > 0;) {
+    const uint32_t count = n < PART ? n : PART;
+    launch(first, count);
+    first += count;
+    n -= count;
+  }
 }
 
 // ------------------------------------------------------------------ internal launchers

@@ -129,7 +129,12 @@ def attention(B, S, H, kv, hd, pad, rope, seed=0, poison=None):
 @pytest.mark.parametrize("B,S,H,kv,hd,pad,rope", [
     (1, 1, 2, 2, 2, 0, True), (2, 15, 2, 1, 16, 0, True), (1, 33, 4, 2, 10, 1, True),
     (2, 64, 4, 4, 32, 0, True), (2, 200, 6, 2, 64, 4, True), (1, 130, 2, 2, 36, 0, False),
-    (1, 300, 2, 1, 128, 0, True), (1, 129, 1, 1, 80, 2, True)])
+    (1, 300, 2, 1, 128, 0, True), (1, 129, 1, 1, 80, 2, True),
+    # sequences that share a block of rows (over 2048 of them times heads): the last
+    # block full, partly full, one sequence in it
+    (1037, 1, 2, 1, 16, 0, True), (2064, 1, 1, 1, 128, 0, True), (521, 2, 4, 2, 64, 0, True),
+    (516, 3, 4, 2, 10, 1, True), (1027, 5, 2, 2, 32, 0, True), (343, 7, 6, 2, 36, 4, True),
+    (684, 8, 3, 3, 80, 0, False), (1027, 9, 2, 1, 16, 0, True)])
 def test_attention(B, S, H, kv, hd, pad, rope):
     banner(f"attention f32 B={B} S={S} H={H}/{kv} hd={hd} pad={pad}")
     got, ref = attention(B, S, H, kv, hd, pad, rope)
@@ -166,10 +171,28 @@ def test_values_not_finite_reach_only_who_sees_them(bad):
     close(d[:at, :hd], d0[:at, :hd].double(), 1e-6)          # dq of other queries
 
 
-def test_attention_more_blocks_than_one_grid_dimension():
-    """2^23 + 5 sequences of 9 tokens, a block of 16 rows each: a grid of two
-    dimensions (one holds fewer than 2^32 work-items, 256 per block). The first, the middle and the last ones
-    against float64."""
+@pytest.mark.parametrize("bad", [math.nan, math.inf])
+def test_values_not_finite_stay_in_their_sequence(bad):
+    """Sequences of 5 tokens share a block of rows: one that holds such values leaves
+    the others as they are (to the order of at most 5 terms, as above)."""
+    banner(f"attention f32, short sequences with {bad}")
+    B, S, hd = 2051, 5, 16
+    clean, _ = attention(B, S, 1, 1, hd, 0, False, seed=5)
+
+    def poison(qkv, dout):
+        qkv[2 * S + 1], dout[2 * S + 1] = bad, bad
+
+    got, _ = attention(B, S, 1, 1, hd, 0, False, seed=5, poison=poison)
+    others = [b for b in range(B) if b != 2]
+    for a, b in zip(got, clean):
+        close(a.reshape(B, -1)[others], b.reshape(B, -1)[others].double(), 1e-6)
+    assert not bool(torch.isfinite(got[0].view(B, S, hd)[2, 1:]).any())
+
+
+def test_attention_more_blocks_than_one_launch_takes():
+    """2^23 + 5 sequences of 9 tokens, a block of 16 rows each: launches in parts (one
+    holds fewer than 2^32 work-items, 256 per block). The first, those around the
+    first part's end and the last ones against float64."""
     B, S, hd = (1 << 23) + 5, 9, 2
     banner(f"attention f32 of {B} sequences")
     g = gen(9)
