@@ -42,6 +42,7 @@ struct F32P {
   int vec_a, vec_b;  // k-major rows of whole 16-byte runs
   uint32_t a_bytes, b_bytes;  // byte extents (ring kernel)
   unsigned tiles_n;
+  unsigned first;  // the launch's first tile
 };
 
 // Which column pair tile column j of a T-wide tile belongs to: RoPE's (i, i +
@@ -292,7 +293,7 @@ __device__ __forceinline__ void ring_block(F32P p, unsigned wg, lds_t *R0) {
 template <int T, int W, bool A_K, bool B_K>
 __global__ __launch_bounds__(64 * W) void gemm_f32_ring_kernel(F32P p) {
   __shared__ __align__(16) char ring[ring_lds<T, W>()];
-  ring_block<T, W, A_K, B_K>(p, blockIdx.x, LDS_AS(char, ring));
+  ring_block<T, W, A_K, B_K>(p, p.first + blockIdx.x, LDS_AS(char, ring));
 }
 
 // An input gradient's nx tiles and a weight gradient's in one grid: the same bits as
@@ -349,7 +350,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(F32P p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
-  const int m0 = (int)(blockIdx.x / p.tiles_n) * T, tn = (int)(blockIdx.x % p.tiles_n);
+  const unsigned wg = p.first + blockIdx.x;
+  const int m0 = (int)(wg / p.tiles_n) * T, tn = (int)(wg % p.tiles_n);
   // rows and columns past the operands read the last valid one (never stored)
   int arow[F], brow[F];
 #pragma unroll
@@ -400,27 +402,31 @@ template <int T>
 lc_status run_f32(F32P p, bool ak, bool bk, bool ring, hipStream_t s) {
   const int cols = p.epi == LC_EPI_SWIGLU ? T / 2 : T;
   const int64_t tm = ((int64_t)p.M + T - 1) / T, tn = ((int64_t)p.N + cols - 1) / cols;
-  if (tm * tn > INT32_MAX / (64 * NW)) return fail(LC_ERR_UNSUPPORTED, "gemm fp32: output too large");
+  if (tm * tn > UINT32_MAX) return fail(LC_ERR_UNSUPPORTED, "gemm fp32: output too large");
   p.tiles_n = (unsigned)tn;
-  const dim3 grid((unsigned)(tm * tn)), block(64 * NW);
-  if (ring) {
-    auto launch = [&](auto w) {
-      constexpr int W = decltype(w)::value;
-      const dim3 blk(64 * W);
-      if (ak && bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, true, true>), grid, blk, 0, s, p);
-      else if (ak) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, true, false>), grid, blk, 0, s, p);
-      else if (bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, false, true>), grid, blk, 0, s, p);
-      else hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, false, false>), grid, blk, 0, s, p);
-    };
-    // (eight waves' stages take a compute unit's LDS for one workgroup)
-    if (T == 32 && tm * tn <= 256) launch(std::integral_constant<int, T == 32 ? 8 : 4>{});
-    else launch(std::integral_constant<int, 4>{});
+  auto run_ring = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    launch_parts((uint32_t)(tm * tn), [&](uint32_t first, uint32_t count) {
+      p.first = first;
+      const dim3 grid(count), block(64 * W);
+      if (ak && bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, true, true>), grid, block, 0, s, p);
+      else if (ak) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, true, false>), grid, block, 0, s, p);
+      else if (bk) hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, false, true>), grid, block, 0, s, p);
+      else hipLaunchKernelGGL((gemm_f32_ring_kernel<T, W, false, false>), grid, block, 0, s, p);
+    });
     return check_launch("gemm_f32_ring_kernel");
-  }
-  if (ak && bk) hipLaunchKernelGGL((gemm_f32_kernel<T, true, true>), grid, block, 0, s, p);
-  else if (ak) hipLaunchKernelGGL((gemm_f32_kernel<T, true, false>), grid, block, 0, s, p);
-  else if (bk) hipLaunchKernelGGL((gemm_f32_kernel<T, false, true>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((gemm_f32_kernel<T, false, false>), grid, block, 0, s, p);
+  };
+  // (eight waves' stages take a compute unit's LDS for one workgroup)
+  if (ring && T == 32 && tm * tn <= 256) return run_ring(std::integral_constant<int, T == 32 ? 8 : 4>{});
+  if (ring) return run_ring(std::integral_constant<int, 4>{});
+  launch_parts((uint32_t)(tm * tn), [&](uint32_t first, uint32_t count) {
+    p.first = first;
+    const dim3 grid(count), block(64 * NW);
+    if (ak && bk) hipLaunchKernelGGL((gemm_f32_kernel<T, true, true>), grid, block, 0, s, p);
+    else if (ak) hipLaunchKernelGGL((gemm_f32_kernel<T, true, false>), grid, block, 0, s, p);
+    else if (bk) hipLaunchKernelGGL((gemm_f32_kernel<T, false, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((gemm_f32_kernel<T, false, false>), grid, block, 0, s, p);
+  });
   return check_launch("gemm_f32_kernel");
 }
 

@@ -57,6 +57,17 @@ def test_products(M, N, K, pad, layout):
     close(C[:, N:], ref * gate.double() * s, 1e-6)
 
 
+def test_more_tiles_than_one_launch_takes():
+    """The widest output the call takes, one row: over 2^23 tiles of 64 columns, in
+    parts. One product per value: exact."""
+    N = (2**31 - 1) // 4
+    banner(f"gemm f32 1x{N}x1")
+    b, c = torch.randn((N, 1), generator=gen(1), device=DEV), torch.zeros((1, N), device=DEV)
+    a = torch.full((4, 1), 0.75, device=DEV)
+    lc.lc_gemm(F32, lc.LC_EPI_STORE, 1, N, 1, a, 1, 1, b, 1, 1, c, N)
+    assert torch.equal(c.view(-1), b.view(-1) * 0.75)
+
+
 @pytest.mark.parametrize("T,f,d", [(5, 3, 7), (128, 344, 128), (400, 1500, 36)])
 def test_gate_up(T, f, d):
     banner(f"gemm f32 swiglu {T} {f} {d}")
