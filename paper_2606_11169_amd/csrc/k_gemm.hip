@@ -570,9 +570,18 @@ static int pick_tile(const lc_gemm_args &a) {
   const int64_t c128 = (tiles(128) + CU - 1) / CU * 85;
   const int64_t c64 = (tiles(64) + CU - 1) / CU * 44;
   const int64_t c32 = (tiles(32) + CU - 1) / CU * 22;
-  if (c32 < c64 && c32 < c128 && c32 < c256) return 32;
-  if (c64 < c128 && c64 < c256) return 64;
-  return c128 < c256 ? 128 : 256;
+  int t = c128 < c256 ? 128 : 256;
+  if (c64 < c128 && c64 < c256) t = 64;
+  if (c32 < c64 && c32 < c128 && c32 < c256) t = 32;
+  // a launch holds fewer than 2^32 work-items (of very wide grouped outputs only the
+  // largest tile's upper bound of workgroups fits)
+  auto fits = [&](int64_t tile) {
+    const int64_t tm = (a.M + tile - 1) / tile + (a.group_mode == LC_GROUP_ROWS ? a.n_groups : 0);
+    const int64_t n = tm * ((N + tile - 1) / tile) * (a.group_mode == LC_GROUP_K ? a.n_groups : 1);
+    return n * (tile >= 128 ? 512 : 256) <= (int64_t)UINT32_MAX;
+  };
+  while (t < 256 && !fits(t)) t *= 2;
+  return t;
 }
 
 // The bf16 kernels' own limits, and their launch parameters.

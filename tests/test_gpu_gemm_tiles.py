@@ -136,3 +136,17 @@ def test_tiles_grouped(sizes, N):
     for e in range(G):
         r = slice(off[e], off[e + 1])
         assert torch.equal(D[e].double(), 1 + X[r].double().t() @ Y[r].double()), e
+
+
+def test_widest_grouped_output():
+    """64 groups, eight of one row each, of 30 million columns: the smaller tiles' upper
+    bound of workgroups passes what a launch takes. Integer operands: exact."""
+    G, N, K = 64, 30_000_000, 8
+    banner(f"gemm tiles grouped 8x{N}x{K}")
+    g = gen(G)
+    A, B = ints(g, 8, K), ints(g, N, K)
+    off = torch.tensor([min(i, 8) for i in range(G + 1)], dtype=torch.int32, device=DEV)
+    C = torch.zeros((8, N), device=DEV)
+    lc.lc_gemm(BF16, lc.LC_EPI_STORE_F32, 8, N, K, A, K, 1, B, K, 1, C, N, group_mode=1, n_groups=G,
+               group_offsets=off, group_stride_b=0)
+    assert torch.equal(C, A.float() @ B.float().t())
