@@ -63,6 +63,9 @@ extern "C" {
  * multiple of 8 when an operand is k-major; M a multiple of 8 when A is not
  * k-major; 16-byte aligned pointers. Other dimensions may be any positive
  * size (edges are masked).
+ * Overlap: no output may overlap an operand A, B (except C with
+ * LC_EPI_SWIGLU in fp32); C may lie over R, and with LC_EPI_SWIGLU_BWD over
+ * aux0, aux1, element for element (the same type and stride).
  */
 /* Grouped modes (n_groups groups; group_offsets is a device array of
  * n_groups + 1 nondecreasing offsets written by an earlier kernel, such as the

@@ -118,7 +118,7 @@ __device__ __forceinline__ void finish(const F32P &p, lds_f *part, const f32x16_
         const float u = sum(r, j + T / 2);
         p.aux0[(int64_t)m * p.ld_aux + n] = v;
         p.aux1[(int64_t)m * p.ld_aux + n] = u;
-        *c = v * sigmoidf_(v) * u;
+        if (p.C) *c = v * sigmoidf_(v) * u;
         break;
       }
       case LC_EPI_ROPE: {
@@ -398,6 +398,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(F32P p) {
   finish<T, NW>(p, LDS_AS(float, part), acc, m0, tn, w, lane);
 }
 
+// silu(gate) * up from the stored gate and up (SwiGLU's C in a launch of its own)
+__global__ __launch_bounds__(256) void swiglu_act_f32_kernel(F32P p) {
+  const int64_t n = (int64_t)p.M * p.N;
+  for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int64_t m = i / p.N, c = i % p.N;
+    const float g = p.aux0[m * p.ld_aux + c];
+    p.C[m * p.ldc + c] = g * sigmoidf_(g) * p.aux1[m * p.ld_aux + c];
+  }
+}
+
 template <int T>
 lc_status run_f32(F32P p, bool ak, bool bk, bool ring, hipStream_t s) {
   const int cols = p.epi == LC_EPI_SWIGLU ? T / 2 : T;
@@ -438,6 +448,7 @@ struct Plan {
   F32P p;
   bool ring;
   int64_t tiles32, tiles64;
+  int64_t a_ext, b_ext;  // the operands' bytes from first to last element
 };
 
 Plan plan_of(const lc_gemm_args &a) {
@@ -479,6 +490,8 @@ Plan plan_of(const lc_gemm_args &a) {
            ae < (int64_t)OOB && be < (int64_t)OOB;
   p.a_bytes = (uint32_t)ae;
   p.b_bytes = (uint32_t)be;
+  r.a_ext = ae;
+  r.b_ext = be;
   return r;
 }
 
@@ -487,11 +500,24 @@ Plan plan_of(const lc_gemm_args &a) {
 lc_status gemm_f32_launch(const lc_gemm_args &a, hipStream_t s) {
   if (a.epilogue == LC_EPI_SWIGLU && !a.b_kmajor)
     return fail(LC_ERR_UNSUPPORTED, "gemm fp32: SwiGLU needs k-major B");
-  const Plan r = plan_of(a);
+  Plan r = plan_of(a);
+  // A C over A or B (the gate and up are stored elsewhere, so a caller may reuse the
+  // memory): written once every workgroup is done reading
+  const char *c0 = static_cast<const char *>(a.C), *c1 = c0 + 4 * ((a.M - 1) * a.ldc + a.N);
+  auto over = [&](const void *x, int64_t bytes) {
+    return c0 < static_cast<const char *>(x) + bytes && static_cast<const char *>(x) < c1;
+  };
+  const bool later = a.epilogue == LC_EPI_SWIGLU && (over(a.A, r.a_ext) || over(a.B, r.b_ext));
+  if (later) r.p.C = nullptr;
   const bool ak = a.a_kmajor != 0, bk = a.b_kmajor != 0;
   // 64 x 64 tiles read half the operand bytes per product; 32 x 32 tiles where
   // those would leave a quarter of the compute units or more without one
-  return r.tiles64 >= 192 ? run_f32<64>(r.p, ak, bk, r.ring, s) : run_f32<32>(r.p, ak, bk, r.ring, s);
+  LC_TRY(r.tiles64 >= 192 ? run_f32<64>(r.p, ak, bk, r.ring, s) : run_f32<32>(r.p, ak, bk, r.ring, s));
+  if (!later) return LC_OK;
+  r.p.C = static_cast<float *>(a.C);
+  const unsigned blocks = (unsigned)std::min<int64_t>((a.M * a.N + 255) / 256, 65535);
+  hipLaunchKernelGGL(swiglu_act_f32_kernel, dim3(blocks), dim3(256), 0, s, r.p);
+  return check_launch("swiglu_act_f32_kernel");
 }
 
 lc_status gemm_f32_pair_launch(const lc_gemm_args &x, const lc_gemm_args &w, hipStream_t s, bool *done) {

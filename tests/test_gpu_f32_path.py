@@ -68,7 +68,7 @@ def test_more_tiles_than_one_launch_takes():
     assert torch.equal(c.view(-1), b.view(-1) * 0.75)
 
 
-@pytest.mark.parametrize("T,f,d", [(5, 3, 7), (128, 344, 128), (400, 1500, 36)])
+@pytest.mark.parametrize("T,f,d", [(5, 3, 7), (128, 344, 128), (400, 1500, 36), (1000, 500, 512)])
 def test_gate_up(T, f, d):
     banner(f"gemm f32 swiglu {T} {f} {d}")
     g = gen(T)
@@ -79,6 +79,13 @@ def test_gate_up(T, f, d):
     close(gate, gr, 1e-6)
     close(up, ur, 1e-6)
     close(act, gr * torch.sigmoid(gr) * ur, 1e-6)
+    if f <= d:  # C over A, with A's rows
+        inplace = x.clone()
+        lc.lc_gemm(F32, lc.LC_EPI_SWIGLU, T, f, d, inplace, d, 1, w, d, 1, inplace, d, aux0=gate, aux1=up, ld_aux=f)
+        close(gate, gr, 1e-6)
+        close(up, ur, 1e-6)
+        close(inplace[:, :f], gr * torch.sigmoid(gr) * ur, 1e-6)
+        assert torch.equal(inplace[:, f:], x[:, f:])
 
 
 @pytest.mark.parametrize("T,H,hd,seq", [(7, 1, 2, 3), (128, 4, 32, 64), (400, 12, 64, 200), (50, 3, 10, 50)])
