@@ -79,6 +79,15 @@ __device__ __forceinline__ void dma16s(i32x4_v rs, lds_t *lds, uint32_t voff, ui
                : "memory", "m0");
 }
 
+// 4 bytes per lane into lds + 4 * lane, the scalar offset part as above
+__device__ __forceinline__ void dma4s(i32x4_v rs, lds_t *lds, uint32_t voff, uint32_t soff) {
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dword %0, %1, %2 offen lds"
+               :
+               : "v"(voff), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(m0)
+               : "memory", "m0");
+}
+
 // at most LEFT of this wave's loads in flight and its LDS reads done, then the
 // workgroup's barrier
 template <int LEFT>

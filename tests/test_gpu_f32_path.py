@@ -29,14 +29,21 @@ def close(got, ref, tol):
 
 @pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (33, 31, 5, 0), (130, 66, 129, 3), (128, 344, 128, 0),
                                        (900, 970, 70, 0), (1030, 1024, 164, 4),
-                                       (36, 40, 8, 0), (400, 768, 516, 0), (1000, 1024, 264, 4)])
+                                       (36, 40, 8, 0), (400, 768, 516, 0), (1000, 1024, 264, 4),
+                                       # 4-byte loads, the thin kernel, registers again
+                                       (1030, 1001, 333, 1), (70, 300, 261, 1), (2113, 2049, 67, 0),
+                                       (2052, 2048, 32, 0), (950, 970, 31, 2), (236, 2860, 16, 0), (600, 500, 3, 0),
+                                       # operands of over 2 GiB: the register kernel
+                                       (33, 35, 70, 2**24 + 3), (1025, 900, 12, 2**20)])
 @pytest.mark.parametrize("layout", [(1, 1), (1, 0), (0, 1), (0, 0)])
 def test_products(M, N, K, pad, layout):
     ak, bk = layout
     banner(f"gemm f32 {M}x{N}x{K} pad {pad} {layout}")
     g = gen(M + N + K)
-    A = torch.randn((M, K + pad) if ak else (K, M + pad), generator=g, device=DEV)
-    B = torch.randn((N, K + pad) if bk else (K, N + pad), generator=g, device=DEV)
+    A = torch.empty((M, K + pad) if ak else (K, M + pad), device=DEV)
+    B = torch.empty((N, K + pad) if bk else (K, N + pad), device=DEV)
+    for X in (A, B):
+        X[:, :max(M, N, K) + 4].normal_(generator=g)
     a = A[:, :K] if ak else A[:, :M].t()
     b = B[:, :K] if bk else B[:, :N].t()
     ref = a.double() @ b.double().t()
