@@ -1111,10 +1111,14 @@ lc_status check_extents(const lc_attn_args &a) {
 // 0.93 (2.4), 0.89 | 0.97 (1.8), 1.02-1.04 | 1.0 (1.67); nb = 8 (S = 2048) 0.80 | 0.94 (1.8),
 // 1.06 | 1.07 (1.4). Below, both grids are even and the second pass over K and V is
 // lost; with up to four blocks of a chain it shows earlier; two blocks (S = 512, 80 heads,
-// ratio 2.1: backward 71 -> 73 us) never gain it back. How the blocks fall on the
-// compute units adds some per cent either way (S = 1664, fp16, 31 heads: forward 44 us
-// -> 41 to 47, backward 132 -> 124; 26 heads 43 -> 32).
+// ratio 2.1: backward 71 -> 73 us) never gain it back. The forward's and dQ's lines lie
+// within the noise of each other: of 150 shapes of 128 to 2048 tokens, none that the rule
+// gives to KG = 2 is slower in the forward, one in the backward (S = 1280, 50 heads, 1%). How
+// the blocks fall on the compute units adds some per cent (S = 1664, fp16: forward of 31
+// heads 44 us -> 39, 30 heads 43 -> 36). One block of 128 queries (S = 128) has no chain to
+// halve: forward 7.2 us, 8.3 with KG = 2 at any number of heads up to 256.
 bool small_grid(int S, unsigned bh) {
+  if (S == QB) return false;
   const unsigned n = (unsigned)(S / KV_ROWS) * bh, nb = (unsigned)((S + ROWS - 1) / ROWS);
   return n <= 256 || (n <= 512 && nb >= 3 && bh * (nb + 1) <= (nb <= 4 ? 220u : 300u));
 }
@@ -1157,7 +1161,9 @@ lc_status bwd_mc(const lc_attn_args &a, hipStream_t s) {
   }
   const unsigned bh = (unsigned)(a.H * a.B), nb = (unsigned)((a.S + ROWS - 1) / ROWS);
   const unsigned n = (unsigned)(a.S / KV_ROWS) * bh;  // blocks of 128 keys, and of 128 queries
-  if (n <= 256 && !grads_over_keys(p)) {
+  // (S = 128, all blocks alike: only where both lists fit the chip at once. 120 heads, bf16:
+  // 25 us one after the other, 19 in one grid; 136 heads 26 and 32)
+  if (n <= (a.S == KV_ROWS ? 128u : 256u) && !grads_over_keys(p)) {
     const int64_t rows = (int64_t)a.B * a.S * a.H;
     hipLaunchKernelGGL(attn_bwd_d_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s, p);
     LC_TRY(check_launch("attn_bwd_d_kernel"));

@@ -21,7 +21,7 @@ def rel(got, ref):
 @pytest.mark.parametrize("dt", ["fp16", "bf16"])
 @pytest.mark.parametrize("B,S,H,kv", [(1, 128, 1, 1), (2, 384, 2, 1), (1, 1152, 3, 3), (2, 1152, 16, 4),
                                       (8, 384, 32, 32),
-                                      (16, 256, 32, 8)])
+                                      (16, 256, 32, 8), (2, 128, 70, 35)])
 def test_both_shapes(B, S, H, kv, dt):
     banner(f"attention grids B={B} S={S} H={H}/{kv} {dt}")
     tdt, ldt = (torch.float16, lc.LC_FP16) if dt == "fp16" else (torch.bfloat16, lc.LC_BF16)
