@@ -137,7 +137,16 @@ struct Tile {
 };
 template <int BM>
 __device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile &t) {
+  // Workgroup wg runs on XCD wg % 8, which gets nwg / 8 tiles; the 128 tile, which reads
+  // its operands twice as often as the 256 tile, in grids of over a round also where nwg is no
+  // multiple of 8 (the first nwg % 8 XCDs take one more: 1044 tiles at K = 4096 161 us, 197 in
+  // launch order, 356 tiles at K = 2048 42 and 58; 259 tiles +-5%, the 256 tile up to 5% slower,
+  // the 64 tile 4%). Not
+  // grouped rows, whose grid is an upper bound: the last XCDs would have nothing to do (60
+  // groups of 10 rows 13 -> 18 us).
   if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
+  else if (BM == 128 && nwg > 264 && p.gmode != LC_GROUP_ROWS)
+    wg = (wg & 7) * (nwg >> 3) + min(wg & 7, nwg & 7) + (wg >> 3);
   t.m_lim = p.M;
   t.kbeg = 0;
   t.kend = p.K;
