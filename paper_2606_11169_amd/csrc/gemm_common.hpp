@@ -123,6 +123,22 @@ struct EpiTypes {
   static constexpr int X = TM == 0 ? -1 : SWI ? LC_FP32 : ROPE ? LC_BF16 : -1;
 };
 
+// The epilogues' arithmetic, with the fused operations written out: left to the compiler,
+// which product of a sum is fused (and so its rounding) differed from kernel to kernel, and
+// a call's result with the tile that it got.
+// RoPE: the pair (x, y) turned by the angle of cosine c and sine s
+__device__ __forceinline__ void rope_pair(float &x, float &y, float c, float s) {
+  const float a = __builtin_fmaf(x, c, -(y * s));
+  y = __builtin_fmaf(y, c, x * s);
+  x = a;
+}
+// SwiGLU backward: gate and up gradients of the activation's gradient v
+__device__ __forceinline__ void swiglu_grad(float v, float g, float u, float &dg, float &du) {
+  const float s = sigmoidf_(g);
+  dg = v * u * s * __builtin_fmaf(g, 1.0f - s, 1.0f);
+  du = v * g * s;
+}
+
 // Where the tile of workgroup wg of nwg lies: false when it has none (uniform across
 // the workgroup). Workgroups are dispatched round-robin over the 8 XCDs; each XCD
 // gets a contiguous run of tiles, walked in groups of p.group tile-rows

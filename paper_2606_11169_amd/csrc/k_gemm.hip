@@ -357,11 +357,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
                 const float cv[4] = {cs[u].x, cs[u].y, cs[u].z, cs[u].w};
                 const float sv[4] = {sn[u].x, sn[u].y, sn[u].z, sn[u].w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const float x = a[e], y = b[e];
-                  a[e] = x * cv[e] - y * sv[e];
-                  b[e] = x * sv[e] + y * cv[e];
-                }
+                for (int e = 0; e < 4; ++e) rope_pair(a[e], b[e], cv[e], sv[e]);
               }
               const int64_t row = (int64_t)m * p.ldc + ncol0 + 4 * q;
               store4_dt(Cp, row, c_dt, a[0], a[1], a[2], a[3]);
@@ -434,11 +430,7 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmP p) {
           const float uv[4] = {y.x, y.y, y.z, y.w};
           float dg[4], du[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float sg = sigmoidf_(gv[e]);
-            dg[e] = o[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));
-            du[e] = o[e] * gv[e] * sg;
-          }
+          for (int e = 0; e < 4; ++e) swiglu_grad(o[e], gv[e], uv[e], dg[e], du[e]);
           ra[u] = make_float4(dg[0], dg[1], dg[2], dg[3]);
           rb[u] = make_float4(du[0], du[1], du[2], du[3]);
         } else if constexpr (LD) {

@@ -122,23 +122,20 @@ __device__ __forceinline__ void finish(const F32P &p, lds_f *part, const f32x16_
     if constexpr (E == LC_EPI_ACCUM_F32 || E == LC_EPI_RESIDUAL) {
       *c = x + v;
     } else if constexpr (E == LC_EPI_SWIGLU_BWD) {
-      const float g = x, u = y, s = sigmoidf_(g);
-      c[0] = v * u * s * (1.0f + g * (1.0f - s));
-      c[p.N] = v * g * s;
+      float dg, du;
+      swiglu_grad(v, x, y, dg, du);
+      c[0] = dg;
+      c[p.N] = du;
     } else if constexpr (E == LC_EPI_SWIGLU) {
       const float u = sum(r, j + T / 2);
       p.aux0[(int64_t)m * p.ld_aux + n] = v;
       p.aux1[(int64_t)m * p.ld_aux + n] = u;
       if (p.C) *c = v * sigmoidf_(v) * u;
     } else if constexpr (E == LC_EPI_ROPE) {
-      const float u = sum(r, j + T / 2);
-      if (n < p.rope_cols) {
-        c[0] = v * x - u * y;
-        c[p.hd / 2] = v * y + u * x;
-      } else {
-        c[0] = v;
-        c[p.hd / 2] = u;
-      }
+      float a = v, b = sum(r, j + T / 2);
+      if (n < p.rope_cols) rope_pair(a, b, x, y);
+      c[0] = a;
+      c[p.hd / 2] = b;
     } else {
       *c = v;
     }

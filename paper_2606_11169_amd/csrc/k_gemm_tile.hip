@@ -302,11 +302,7 @@ __device__ __forceinline__ void tile_block(GemmP p, int wg, int nwg, lds_t *R0) 
           const float4 sn = *reinterpret_cast<const float4 *>(p.rsin + ta);
           const float cv[4] = {cs.x, cs.y, cs.z, cs.w}, sv[4] = {sn.x, sn.y, sn.z, sn.w};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float xx = a[e], yy = b[e];
-            a[e] = xx * cv[e] - yy * sv[e];
-            b[e] = xx * sv[e] + yy * cv[e];
-          }
+          for (int e = 0; e < 4; ++e) rope_pair(a[e], b[e], cv[e], sv[e]);
         }
         store4_dt(tile.C, oc, c_dt, a[0], a[1], a[2], a[3]);
         store4_dt(tile.C, oc + 64, c_dt, b[0], b[1], b[2], b[3]);
@@ -329,11 +325,7 @@ __device__ __forceinline__ void tile_block(GemmP p, int wg, int nwg, lds_t *R0) 
       const float uv[4] = {y[it].x, y[it].y, y[it].z, y[it].w};
       float dg[4], du[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float sg = sigmoidf_(gv[e]);
-        dg[e] = v[e] * uv[e] * sg * (1.0f + gv[e] * (1.0f - sg));
-        du[e] = v[e] * gv[e] * sg;
-      }
+      for (int e = 0; e < 4; ++e) swiglu_grad(v[e], gv[e], uv[e], dg[e], du[e]);
       store4_dt(tile.C, oc, c_dt, dg[0], dg[1], dg[2], dg[3]);
       store4_dt(tile.C, oc + p.N, c_dt, du[0], du[1], du[2], du[3]);
     } else if constexpr (EPI == LC_EPI_ACCUM_F32) {

@@ -111,6 +111,54 @@ def test_tiles_rope(T, H, seq):
     assert rel(qb.view(T, 3 * H, 128), ref) < 2 ** -8
 
 
+def test_epilogues_round_alike_on_every_tile():
+    """RoPE, SwiGLU and the SwiGLU backward of 1480, 520, 40 and 20 rows (256, 128, 64 and 32
+    tiles): exact sums, so the same rows get the same bits."""
+    banner("gemm tiles, epilogue bits")
+    g = gen(7)
+    T, N, K = 1480, 6144, 72
+    x, w = ints(g, T, K), ints(g, 2 * N, K)
+    ang = torch.rand((T, 64), generator=g, device=DEV) * 6
+    cos, sin = torch.cos(ang), torch.sin(ang)
+    gate, up = (torch.randn((T, N), generator=g, device=DEV) for _ in range(2))
+
+    def rope(rows, types):
+        q, qb = (torch.empty((rows, N), dtype=t[0], device=DEV) for t in types)
+        lc.lc_gemm(BF16, lc.LC_EPI_ROPE, rows, N, K, x, K, 1, w, K, 1, q, N, aux0=qb, ld_aux=N, rope_cos=cos,
+                   rope_sin=sin, rope_seq=T, rope_cols=N // 2, head_dim=128, c_dtype=types[0][1],
+                   aux_dtype=types[1][1])
+        return q, qb
+
+    def swiglu(rows, c, aux):
+        h = N // 2
+        act = torch.empty((rows, h), dtype=c[0], device=DEV)
+        a0, a1 = (torch.empty((rows, h), dtype=aux[0], device=DEV) for _ in range(2))
+        lc.lc_gemm(BF16, lc.LC_EPI_SWIGLU, rows, h, K, x, K, 1, w, K, 1, act, h, aux0=a0, aux1=a1, ld_aux=h,
+                   c_dtype=c[1], aux_dtype=aux[1])
+        return act, a0, a1
+
+    def swiglu_bwd(rows, c, nt):
+        b = w[:N] if nt else w[:N].t().contiguous()
+        da = torch.empty((rows, 2 * N), dtype=c[0], device=DEV)
+        lc.lc_gemm(BF16, lc.LC_EPI_SWIGLU_BWD, rows, N, K, x, K, 1, b, b.shape[1], int(nt), da, 2 * N, aux0=gate,
+                   aux1=up, ld_aux=N, c_dtype=c[1], aux_dtype=FP32)
+        return (da,)
+
+    f32, f16, b16 = (torch.float32, FP32), (torch.float16, FP16), (torch.bfloat16, BF16)
+    for call in (lambda r: rope(r, (f16, b16)), lambda r: rope(r, (f32, f32)), lambda r: swiglu(r, b16, f32),
+                 lambda r: swiglu(r, f32, f16), lambda r: swiglu_bwd(r, b16, False),
+                 lambda r: swiglu_bwd(r, f32, False), lambda r: swiglu_bwd(r, b16, True)):
+        full = call(T)
+        for rows in (520, 40, 20):
+            for a, b in zip(call(rows), full):
+                assert torch.equal(a, b[:rows])
+    # and the values: the stage's types against float64
+    (da,) = swiglu_bwd(T, f32, True)
+    v, sg = x.double() @ w[:N].double().t(), torch.sigmoid(gate.double())
+    assert rel(da[:, :N], v * up.double() * sg * (1 + gate.double() * (1 - sg))) < 1e-6
+    assert rel(da[:, N:], v * gate.double() * sg) < 1e-6
+
+
 @pytest.mark.parametrize("sizes,N", [([30, 0, 50, 1], 72), ([300, 0, 17, 512, 256, 1], 264),
                                      ([900, 40, 0, 700], 1416)], ids=["32", "64", "128"])
 def test_tiles_grouped(sizes, N):
