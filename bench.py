@@ -224,15 +224,24 @@ def wgrad_roofline(times):
             "timing": "HIP events around each launch inside the timed steps"}
 
 
-GEMM_SRC = os.path.join(ROOT, "paper_2606_11169_amd", "csrc", "k_gemm.hip")
+CSRC = os.path.join(ROOT, "paper_2606_11169_amd", "csrc")
+GEMM_SRCS = ("k_gemm.hip", "gemm_common.hpp", "common.hpp")  # the kernel and what it includes
 TRAFFIC_MD = os.path.join(ROOT, "profiles", "gemm_wgrad_traffic.md")
 CAL_N = 1 << 26  # calibration: accumulate of 2^26 fp32 elements reads 8 B and writes 4 B each
 
 
-def gemm_source_hash() -> str:
+def _digest(d, names) -> str:
     import hashlib
-    with open(GEMM_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in names:
+        with open(os.path.join(d, name), "rb") as f:
+            h.update(name.encode() + b"\0" + f.read())
+    return h.hexdigest()[:16]
+
+
+def gemm_source_hash(d=CSRC) -> str:
+    """Digest of the GEMM kernel's sources (tile walk, loads and padding are in the header)."""
+    return _digest(d, GEMM_SRCS)
 
 
 def measured_traffic():
@@ -255,16 +264,9 @@ def measured_traffic():
 MFMA_MD = os.path.join(ROOT, "profiles", "stage7b_mfma_busy.md")
 
 
-def csrc_hash() -> str:
-    """Digest of every HIP source of the library (the counters depend on all kernels)."""
-    import hashlib
-    h = hashlib.sha256()
-    d = os.path.join(ROOT, "paper_2606_11169_amd", "csrc")
-    for name in sorted(os.listdir(d)):
-        if name.endswith(".hip"):
-            with open(os.path.join(d, name), "rb") as f:
-                h.update(name.encode() + b"\0" + f.read())
-    return h.hexdigest()[:16]
+def csrc_hash(d=CSRC) -> str:
+    """Digest of every HIP source and header of the library (the counters depend on all kernels)."""
+    return _digest(d, sorted(n for n in os.listdir(d) if n.endswith((".hip", ".hpp"))))
 
 
 def measured_mfma_busy():

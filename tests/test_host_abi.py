@@ -388,3 +388,34 @@ def test_bench_reads_the_committed_counter_summaries():
     assert b is None or (0 < b["value"] < 1 and b["source"] == "profiles/stage7b_mfma_busy.md"
                          and b["csrc_sha256_16"] == bench.csrc_hash())
     assert len(bench.csrc_hash()) == 16 and len(bench.gemm_source_hash()) == 16
+
+
+def test_bench_counter_digests_cover_the_headers(tmp_path):
+    """A change of any kernel source or header changes the step's digest; of the GEMM's
+    source or a header that it includes, the GEMM's too."""
+    import importlib.util
+    import pathlib
+    import re
+    import shutil
+    root = pathlib.Path(__file__).resolve().parents[1]
+    spec = importlib.util.spec_from_file_location("bench_mod", root / "bench.py")
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    csrc = tmp_path / "csrc"
+    shutil.copytree(root / "paper_2606_11169_amd" / "csrc", csrc)
+
+    def includes(name):
+        found = [i for i in re.findall(r'#include "([^"]+)"', (csrc / name).read_text()) if (csrc / i).exists()]
+        return {name}.union(*(includes(i) for i in found))
+
+    gemm = includes("k_gemm.hip") - {"host_core.hpp"}  # (declarations of the host core only)
+    assert set(bench.GEMM_SRCS) == gemm
+    step, prod = bench.csrc_hash(str(csrc)), bench.gemm_source_hash(str(csrc))
+    for f in sorted(csrc.iterdir()):
+        if f.suffix not in (".hip", ".hpp"):
+            continue
+        text = f.read_text()
+        f.write_text(text + "\n")
+        assert bench.csrc_hash(str(csrc)) != step, f.name
+        assert (bench.gemm_source_hash(str(csrc)) != prod) == (f.name in gemm), f.name
+        f.write_text(text)
