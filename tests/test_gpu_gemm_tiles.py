@@ -1,7 +1,10 @@
-"""The bf16 GEMM's output tiles (256, 128, 64 and 32, chosen by the output's size)
-at the edges of tiles, rings and k-steps: every layout and epilogue against
-float64 products of the same operands. Integer-valued operands make the plain
-products exact in fp32 (|sum| < 2^24), so those are compared bit for bit."""
+"""The bf16 GEMM's output tiles (256, 128, 64 and 32, chosen by the product's size)
+at the edges of tiles, rings and k-steps, against float64 products of the same
+operands: the plain and accumulating products in every layout on every tile, the
+residual add on every tile, the SwiGLU and RoPE epilogues on every tile and (the
+rounding test) with other element types than the stages'. Integer-valued operands
+make the plain products exact in fp32 (|sum| < 2^24), so those are compared bit for
+bit."""
 import numpy as np
 import pytest
 import torch
@@ -86,6 +89,25 @@ def test_tiles_swiglu_and_residual(T, f, d):
     dact = dy.double() @ w2.double()
     assert rel(da[:, :f], dact * ur * sg * (1 + gr * (1 - sg))) < 2 ** -9
     assert rel(da[:, f:], dact * gr * sg) < 2 ** -9
+
+
+@pytest.mark.parametrize("types", ["fp32", "bf16 residual", "bf16 result"])
+@pytest.mark.parametrize("T,N,K", [(20, 264, 64), (520, 520, 320), (1003, 1928, 960), (1480, 6152, 328)])
+def test_tiles_residual(T, N, K, types):
+    """The residual add, ragged both ways: the sums are exact; one fp32 rounding, and one
+    to bf16 (2^-9 relative) where the result is bf16."""
+    banner(f"gemm tiles residual {T}x{N}x{K} {types}")
+    g = gen(T + N)
+    a, w = ints(g, T, K), ints(g, N, K)
+    h = torch.randn((T, N), generator=g, device=DEV)
+    h = h.to(torch.bfloat16) if types == "bf16 residual" else h
+    y = torch.full((T + 1, N), -3.0, dtype=torch.bfloat16 if types == "bf16 result" else torch.float32, device=DEV)
+    lc.lc_gemm(BF16, lc.LC_EPI_RESIDUAL, T, N, K, a, K, 1, w, K, 1, y, N, R=h, ldr=N,
+               c_dtype=BF16 if types == "bf16 result" else FP32,
+               r_dtype=BF16 if types == "bf16 residual" else FP32)
+    ref = h.double() + a.double() @ w.double().t()
+    assert rel(y[:T], ref) < (2 ** -9 if types == "bf16 result" else 1e-6)
+    assert bool((y[T] == -3.0).all())
 
 
 @pytest.mark.parametrize("T,H,seq", [(40, 1, 8), (520, 2, 130), (1003, 5, 59), (1480, 16, 1480)])
