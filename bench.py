@@ -225,7 +225,7 @@ def wgrad_roofline(times):
 
 
 CSRC = os.path.join(ROOT, "paper_2606_11169_amd", "csrc")
-GEMM_SRCS = ("k_gemm.hip", "gemm_common.hpp", "common.hpp")  # the kernel and what it includes
+GEMM_SRCS = ("k_gemm.hip", "gemm_common.hpp", "lds_dma.hpp", "common.hpp")  # the kernel and what it includes
 TRAFFIC_MD = os.path.join(ROOT, "profiles", "gemm_wgrad_traffic.md")
 CAL_N = 1 << 26  # calibration: accumulate of 2^26 fp32 elements reads 8 B and writes 4 B each
 

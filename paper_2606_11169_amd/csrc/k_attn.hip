@@ -41,7 +41,7 @@
 // per-lane base plus an immediate offset (no per-read address arithmetic). An
 // earlier layout XOR-swizzled the chunks of each row across the lanes of a
 // load, which needed an XOR and an add per transposing read.
-#include "common.hpp"
+#include "lds_dma.hpp"
 
 #include <math.h>
 
@@ -66,11 +66,6 @@ constexpr float LN2 = 0.6931471805599453f;
 constexpr int RUNB = 1024 + 16;
 constexpr int TILE = 16 * RUNB;
 
-typedef __attribute__((ext_vector_type(4))) int i32x4_v;
-typedef __attribute__((ext_vector_type(4))) short s16x4_v;
-typedef __attribute__((address_space(3))) char lds_t;
-#define LDS_AS(T, ptr) ((__attribute__((address_space(3))) T *)(ptr))
-
 template <typename E> struct V8;
 template <> struct V8<__bf16> { typedef bf16x8_v type; };
 template <> struct V8<_Float16> { typedef f16x8_v type; };
@@ -86,44 +81,6 @@ __device__ __forceinline__ f32x16_v mfma(f16x8_v a, f16x8_v b, f32x16_v c) {
 // load run of tile row r (an involution on 0..15: run q holds rows swz(q) + 16 p)
 __device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
 __device__ __forceinline__ int tile_off(int r, int c) { return swz(r & 15) * RUNB + (r >> 4) * 256 + c * 16; }
-
-__device__ __forceinline__ i32x4_v make_rsrc(const void *base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  i32x4_v r;
-  r[0] = __builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-  r[1] = __builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xFFFFu));
-  r[2] = __builtin_amdgcn_readfirstlane((int)bytes);
-  r[3] = 0x00020000;
-  return r;
-}
-
-// 16 bytes per lane from byte offset `off` of the buffer into LDS at
-// lds + 16 * lane (inline assembly: the compiler does not track it; the
-// block loop's explicit wait before its barrier orders it)
-__device__ __forceinline__ void dma16(i32x4_v rs, lds_t *lds, uint32_t off) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(off), "s"(rs), "s"(m0)
-               : "memory", "m0");
-}
-// the same with a wave-uniform part of the offset in the instruction's scalar
-// offset (every access in range: the callers' tiles lie inside their buffers)
-__device__ __forceinline__ void dma16s(i32x4_v rs, lds_t *lds, uint32_t voff, uint32_t soff) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :
-               : "v"(voff), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(soff)), "s"(m0)
-               : "memory", "m0");
-}
-// 4 bytes per lane into lds + 4 * lane
-__device__ __forceinline__ void dma4(i32x4_v rs, lds_t *lds, uint32_t off) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t) reinterpret_cast<uintptr_t>(lds));
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dword %0, %1, 0 offen lds"
-               :
-               : "v"(off), "s"(rs), "s"(m0)
-               : "memory", "m0");
-}
 
 // Run `run` (0..15) of a [64][128] tile: rows swz(run) + 16 p (p = 0..3) of a
 // block of 64 rows, each 16-lane group reading one row's 256 bytes in address
@@ -499,10 +456,10 @@ __device__ __forceinline__ void store_row_t(__bf16 *row, const f32x16_v (&acc)[4
 
 // dQ: one workgroup per 256 queries; LDS stage = K (QE) | V (bf16), plus the
 // bf16 rows of K for fp16 inputs. Each query's D = dO.O is formed here from
-// the dO row the lane pair holds and written out for the dK/dV kernel.
-// KG = 2 (small grids, as in the forward):
-// 128 queries, waves w and w + 4 own the same 32 and take the two halves of every
-// key block; their sums are added through LDS (16 heads of 2048: 95 -> 69 us).
+// the dO row the lane pair holds and written out for the dK/dV kernel. KG = 2 (small
+// grids, as in the forward): 128 queries, waves w and w + 4 own the same 32 and take
+// the two halves of every key block; their sums are added through LDS (16 heads of
+// 2048: 95 -> 69 us).
 template <typename QE> constexpr int dq_smem() { return 2 * (std::is_same<QE, __bf16>::value ? 2 : 3) * TILE; }
 // One workgroup's part: query block `index` of the grid's order; HAVE_D: D and
 // -lse log2(e) are written already.
@@ -923,12 +880,12 @@ __global__ __launch_bounds__(256) void attn_bwd_d_kernel(AttnP p) {
 
 // dQ (128 queries per workgroup, KG = 2) and dK/dV in one grid, for grids of at most
 // one workgroup of each per compute unit, which would last as long as their longest
-// causal block one after the other: eight blocks of the one, eight of the other (one per XCD), each list
-// heaviest first, so that the one's short blocks fill the chip beside the other's
-// long ones. D and -lse log2(e) are written before by attn_bwd_d_kernel. Backward of
-// 4 heads of 256: 36 -> 21 us, 16 heads of 2048 (256 blocks each) 116 -> 93; with
-// more blocks each list evens itself out and the extra pass is lost (16 heads of 2 x
-// 1920, 480 blocks: 159 -> 169).
+// causal block one after the other: eight blocks of the one, eight of the other (one
+// per XCD), each list heaviest first, so that the one's short blocks fill the chip
+// beside the other's long ones. D and -lse log2(e) are written before by
+// attn_bwd_d_kernel. Backward of 4 heads of 256: 36 -> 21 us, 16 heads of 2048 (256
+// blocks each) 116 -> 93; with more blocks each list evens itself out and the extra
+// pass is lost (16 heads of 2 x 1920, 480 blocks: 159 -> 169).
 template <typename QE>
 __global__ __launch_bounds__(NT) void attn_bwd_both_kernel(AttnP p) {
   constexpr int BYTES = dkdv_smem<QE>() > dq_smem<QE>() ? dkdv_smem<QE>() : dq_smem<QE>();

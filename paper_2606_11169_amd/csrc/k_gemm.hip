@@ -60,7 +60,8 @@
 // 64) that RoPE and SwiGLU combine sit in one wave (blocks j and j + 4).
 // Output, residual and gate/up element types are run-time values (uniform
 // branches in the epilogue only), except in the instantiations for the decoder
-// stage's own type mix (EpiTypes below), where they are compile-time constants.
+// stage's own type mix (EpiTypes in gemm_common.hpp), where they are compile-time
+// constants.
 #include "gemm_common.hpp"
 
 namespace lc {
@@ -89,17 +90,16 @@ constexpr int STAGE_BYTES = 2 * OPND_BYTES;   // A | B
 template <bool KMAJ, int ROWMAP>
 struct Stream {
   uint32_t base;     // byte offset of run 0's row (k-major) or k row (m/n-major)
-  uint32_t col[2];   // byte offset inside the row for even / odd runs
+  uint32_t col;      // byte offset inside the row
   uint32_t run;      // byte distance between two rows (k-major) or k rows
   uint32_t kb;       // bytes per unit of k
   uint32_t rows;     // bit t set when run t's row / columns are inside the operand
-  int kl[2];         // k-major: first k of this lane's chunk; m/n-major: k row
-                     // of run 0 (both entries equal)
+  int kl;            // k-major: first k of this lane's chunk; m/n-major: k row of run 0
 
   __device__ __forceinline__ void init(int64_t ld, int base_row, int lim, int wave, int lane) {
     if constexpr (KMAJ) {
       const int pos = lane >> 3;  // the lane's row position inside each run
-      kl[0] = kl[1] = 8 * (lane & 7);
+      kl = 8 * (lane & 7);
       int grow0, oc0;
       if constexpr (ROWMAP == 0) {
         grow0 = base_row + 8 * wave + 32 * pos;
@@ -114,7 +114,7 @@ struct Stream {
 #pragma unroll
       for (int t = 0; t < 8; ++t) rows |= (oc0 + t < lim ? 1u : 0u) << t;
       base = rows ? (uint32_t)((int64_t)grow0 * ld * 2) : 0u;
-      col[0] = col[1] = (uint32_t)(kl[0] * 2);
+      col = (uint32_t)(kl * 2);
       run = (uint32_t)(ld * 2);
       kb = 2;
     } else {
@@ -122,10 +122,10 @@ struct Stream {
       // k row of run 0: run q holds k rows swap23(q) and swap23(q) + 32
       const int kr0 = 4 * (wave & 1) + 16 * (wave >> 1) + 32 * (lane >> 5);
       const int gm = base_row + 8 * (lane & 31);    // first of the lane's 8 columns
-      kl[0] = kl[1] = kr0;
+      kl = kr0;
       rows = gm < lim ? 0xFFu : 0u;
       base = (uint32_t)((int64_t)kr0 * ld * 2);
-      col[0] = col[1] = gm < lim ? (uint32_t)(gm * 2) : 0u;
+      col = gm < lim ? (uint32_t)(gm * 2) : 0u;
       run = (uint32_t)(ld * 2);
       kb = (uint32_t)(ld * 2);
     }
@@ -138,15 +138,15 @@ struct Stream {
   __device__ __forceinline__ void offsets(uint32_t vo[8], int k0) const {
 #pragma unroll
     for (int t = 0; t < 8; ++t)
-      vo[t] = (rows >> t) & 1u ? base + step(t) * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
+      vo[t] = (rows >> t) & 1u ? base + step(t) * run + col + (uint32_t)k0 * kb : OOB;
   }
   // run t of the wave's 8 runs of the stage starting at k0, into `lds` (the
   // operand's stage), every lane checked against K
   __device__ __forceinline__ void load1(i32x4_v rs, lds_t *lds, int wave, int k0, int K, int t) const {
     bool ok = (rows >> t) & 1u;
-    if constexpr (KMAJ) ok = ok && k0 + kl[t & 1] < K;
-    else ok = ok && k0 + kl[0] + (int)step(t) < K;
-    const uint32_t off = ok ? base + step(t) * run + col[t & 1] + (uint32_t)k0 * kb : OOB;
+    if constexpr (KMAJ) ok = ok && k0 + kl < K;
+    else ok = ok && k0 + kl + (int)step(t) < K;
+    const uint32_t off = ok ? base + step(t) * run + col + (uint32_t)k0 * kb : OOB;
     dma16(rs, lds + (8 * wave + t) * RUN, off);
   }
 };
@@ -700,8 +700,9 @@ lc_status gemm_launch(const lc_gemm_args &a, hipStream_t s) {
 // An input gradient x and a weight gradient w of one backward step that do not depend
 // on each other: one launch where both are products of 32 or 64 tiles (bf16) or
 // eight-wave 32 tiles (fp32), which leave most of the chip idle (small bf16 step 1012 ->
-// 955 us, tiny fp32 step 797 -> 648); larger tiles keep a launch each, as a 128 or 256
-// tile has another workgroup size. The results are those of the two launches.
+// 955 us, tiny fp32 step 797 -> 648). A 128 or 256 tile has workgroups of 512 threads, the
+// 64 and 32 tiles of 256; two products of the larger ones could share a launch, but fill
+// the chip by themselves more often. The results are those of the two launches.
 lc_status gemm_pair_launch(const lc_gemm_args &x, const lc_gemm_args &w, hipStream_t s) {
   const bool form = x.dtype == w.dtype && x.group_mode == LC_GROUP_NONE && w.group_mode == LC_GROUP_NONE &&
                     x.a_kmajor && !x.b_kmajor && !w.a_kmajor && !w.b_kmajor &&

@@ -6,18 +6,18 @@
 // one tile: with few tiles per compute unit there is no second workgroup to
 // cover a stage's load latency. So k is split inside the workgroup as well:
 // every wave owns a block of the tile for its own k-steps of each stage (the 128
-// tile: 8 waves = 2 x 2 blocks of 64 x 64 x 2 k-steps of a 64-deep stage; the 64 and
-// 32 tiles: 4 waves, the whole tile each, one k-step of a 128-deep or two of a
-// 256-deep stage), which halves (quarters) the
-// chain, reads no operand row of the smaller tiles twice from LDS, and keeps both
-// (one) waves of a SIMD busy; the waves' partial tiles are added in k-step order
-// in the epilogue, through LDS. (At 2048 x 2048 x 11264 the 128 tile runs at 1040
-// TFLOP/s with one tile per compute unit; 64 tiles of 256 x 256 at 473. The 64
-// tile takes 9 us for a 256 x 512 x 1408 product, the 256 tile 31; the 32 tile, with
-// four times the compute units loading, 6.) Operands stream HBM->LDS through a ring of four
-// stages, three stages ahead of the one being multiplied (the 256 tile's two 64
-// KiB stages leave no room for that; here a stage is 32 KiB), one barrier per
-// stage, the next stage's fragments read while one multiplies.
+// tile: 8 waves = 2 x 2 blocks of 64 x 64 x 2 k-steps of a 64-deep stage; the 64
+// and 32 tiles: 4 waves, the whole tile each, one k-step of a 128-deep or two of a
+// 256-deep stage). That halves (quarters) the chain, reads no operand row of the
+// smaller tiles twice from LDS, and keeps both (one) waves of a SIMD busy; the
+// waves' partial tiles are added in k-step order in the epilogue, through LDS. (At
+// 2048 x 2048 x 11264 the 128 tile runs at 1040 TFLOP/s with one tile per compute
+// unit; 64 tiles of 256 x 256 at 473. The 64 tile takes 9 us for a 256 x 512 x 1408
+// product, the 256 tile 31; the 32 tile, with four times the compute units loading,
+// 6.) Operands stream HBM->LDS through a ring of four stages, three stages ahead of
+// the one being multiplied (the 256 tile's two 64 KiB stages leave no room for that;
+// here a stage is 32 KiB), one barrier per stage, the next stage's fragments read
+// while one multiplies.
 #include "gemm_common.hpp"
 
 namespace lc {

@@ -6,20 +6,20 @@
 //             dg_k += sum_t dn_tk xh_tk
 //
 // Forward: 8 elements per lane per step (16- or 32-byte accesses); rows of up to
-// 4096 elements stay in one wave's registers between the row's
-// reduction and its write, up to 8192 in two waves'; longer rows are read twice (the
-// second read hits L2; 3001 rows of 5120: 24 us that way, 20 in registers). Backward: rows of up to 8192 elements stay in registers, split
-// over one to eight waves by their length; longer rows go one per wave, read
-// twice (3001 rows of 5120: 134 us that way with its own partial-sum pass, 67 in
-// registers). Every tensor's element type is a run-time
-// value (uniform branches), except in the instantiations for the stages' own
-// type mixes, where the types are template arguments (straight-line
-// loads: 20-25% faster forward, 9% faster backward rows). The gain gradient is a column reduction over
-// rows: each backward workgroup handles kNormRowsPerBlock rows and writes
-// the fp32 partial sums of its rows in a fixed order, then the final kernel
-// adds the partials of each column: sixteen slices of consecutive blocks,
-// each summed in block order, then the slices in order — the same order on
-// every run, no atomics.
+// 4096 elements stay in one wave's registers between the row's reduction and its
+// write, rows of up to 8192 in two waves'; longer rows are read twice (the second
+// read hits L2; 3001 rows of 5120: 24 us that way, 20 in registers). Backward: rows
+// of up to 8192 elements stay in registers, split over one to eight waves by their
+// length; longer rows go one per wave, read twice (3001 rows of 5120: 134 us that
+// way with its own partial-sum pass, 67 in registers). Every tensor's element type is
+// a run-time value (uniform branches), except in the instantiations for the stages'
+// own type mixes, where the types are template arguments (straight-line loads:
+// 20-25% faster forward, 9% faster backward rows). The gain gradient is a column
+// reduction over rows: each backward workgroup handles kNormRowsPerBlock rows and
+// writes the fp32 partial sums of its rows in a fixed order, then the final kernel
+// adds the partials of each column: sixteen slices of consecutive blocks, each
+// summed in block order, then the slices in order (the same order on every run, no
+// atomics).
 #include "common.hpp"
 
 #include <mutex>
@@ -29,8 +29,8 @@ namespace {
 
 constexpr int ROWS_PER_BLOCK = 4;  // forward: rows of one wave each
 constexpr int MAXU = 8;            // 8-element chunks per lane held in registers
-constexpr int MAXD = 64 * 8 * MAXU;  // longest row the forward keeps in registers
-constexpr int MAXB = 8192;           // longest row the backward keeps in registers
+constexpr int MAXD = 64 * 8 * MAXU;  // longest row that one forward wave holds
+constexpr int MAXB = 8192;           // longest row kept in registers, both directions
 
 struct NormP {
   const void *x, *g, *dn, *dres;
@@ -156,9 +156,10 @@ __device__ __forceinline__ void bwd_row_long(const NormP &p, int64_t row, int la
 //
 // A workgroup's chain of loads and reductions is one iteration long per 16 / WPR
 // rows, so a row gets as few waves as hold it: one up to 512 values (all sixteen
-// rows at once; with four waves per row whatever its length, 128 rows of 128
-// took 12 us, with one and the slots added in one step 4), then WPR = 2, 4 with one chunk per lane, 4 and 8 with two (16
-// values per lane of each tensor, so that four waves per SIMD stay resident).
+// rows at once; with four waves per row whatever its length, 128 rows of 128 took 12
+// us, with one and the slots added in one step 4), then WPR = 2, 4 with one chunk per
+// lane, 4 and 8 with two (16 values per lane of each tensor, so that four waves per
+// SIMD stay resident).
 constexpr int BW_THREADS = 1024;
 template <int WPR, int U, int DNDT, int XDT, int WDT, int RDT, int ODT>
 __global__ __launch_bounds__(BW_THREADS) void rmsnorm_bwd_rows_kernel(NormP p) {
