@@ -325,11 +325,35 @@ def adam_traffic():
     return float(vals["traffic_bytes_per_launch"])
 
 
+def time_in_turn(torch, stream, sides, reps, rounds=7):
+    """{name: microseconds per launch} of the functions in `sides`: after a warm-up of all,
+    `rounds` rounds of `reps` launches back to back between two HIP events for each side in
+    turn (per-launch events would add each call's host-side launch gap), the median round.
+    In turn, because the clock under load settles over tens of milliseconds: whichever side
+    were measured first by itself would run at another clock."""
+    def once(fn):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record(stream)
+        for _ in range(reps):
+            fn()
+        e1.record(stream)
+        e1.synchronize()
+        return e0.elapsed_time(e1) * 1e3 / reps
+
+    us = {name: [] for name in sides}
+    with torch.cuda.stream(stream):
+        for r in range(rounds + 3):
+            for name, fn in sides.items():
+                t = once(fn)
+                if r >= 3:
+                    us[name].append(t)
+    return {name: sorted(t)[len(t) // 2] for name, t in us.items()}
+
+
 def gemm_compare(torch, lc, stream, reps=20, n=4096):
     """Diagnostic: the library's GEMM and hipBLASLt (torch.matmul; the library never calls
     it) on one n^3 product C = A B^T of N(0, 1) bf16 operands, both k-major (the layout of
-    the stage's forward products), bf16 output; `reps` launches back to back between two
-    HIP events (per-launch events would add each call's host-side launch gap)."""
+    the stage's forward products), bf16 output; both sides in turn (time_in_turn)."""
     g = torch.Generator(device="cuda")
     g.manual_seed(0)
     a = torch.randn(n, n, generator=g, device="cuda").to(torch.bfloat16)
@@ -343,20 +367,8 @@ def gemm_compare(torch, lc, stream, reps=20, n=4096):
         torch.matmul(a, b.t(), out=c)
 
     out = {"workload": f"gemm_nt_{n}^3_bf16", "flop": 2 * n ** 3}
-    with torch.cuda.stream(stream):
-        for name, fn in (("lc_gemm", lib), ("hipblaslt", blas)):
-            for _ in range(3):
-                fn()
-            stream.synchronize()
-            e0 = torch.cuda.Event(enable_timing=True)
-            e1 = torch.cuda.Event(enable_timing=True)
-            e0.record(stream)
-            for _ in range(reps):
-                fn()
-            e1.record(stream)
-            e1.synchronize()
-            ms = e0.elapsed_time(e1) / reps
-            out[name] = {"us": round(ms * 1e3, 1), "tflops": round(2 * n ** 3 / (ms * 1e-3) / 1e12, 1)}
+    for name, us in time_in_turn(torch, stream, {"lc_gemm": lib, "hipblaslt": blas}, reps).items():
+        out[name] = {"us": round(us, 1), "tflops": round(2 * n ** 3 / (us * 1e-6) / 1e12, 1)}
     return out
 
 
@@ -364,7 +376,7 @@ def gemm_compare_shapes(torch, lc, cfg, stream, reps=10):
     """Diagnostic: the library's GEMM main loop (plain bf16 store; the stage's fused
     epilogues left out so both sides do the same work) and hipBLASLt (torch.matmul; the
     library never calls it) at the stage's twelve product shapes and layouts, N(0, 1)
-    bf16 operands; `reps` launches back to back between two HIP events per side.
+    bf16 operands; both sides in turn (time_in_turn).
     Layouts as C = A B^T: NT = both operands k-major (forward projections), NN = B
     m/n-major (input gradients), TN = both m/n-major (weight gradients)."""
     T, d, f = cfg.tokens, cfg.d_model, cfg.d_ff
@@ -397,26 +409,14 @@ def gemm_compare_shapes(torch, lc, cfg, stream, reps=10):
         def blas():
             torch.matmul(*blas_ab, out=c)
         row = {"product": name, "layout": lay, "M": M, "N": N, "K": K}
-        with torch.cuda.stream(stream):
-            for side, fn in (("lc_gemm", lib), ("hipblaslt", blas)):
-                for _ in range(3):
-                    fn()
-                stream.synchronize()
-                e0 = torch.cuda.Event(enable_timing=True)
-                e1 = torch.cuda.Event(enable_timing=True)
-                e0.record(stream)
-                for _ in range(reps):
-                    fn()
-                e1.record(stream)
-                e1.synchronize()
-                ms = e0.elapsed_time(e1) / reps
-                row[side] = {"us": round(ms * 1e3, 1), "tflops": round(2 * M * N * K / (ms * 1e-3) / 1e12, 1)}
+        for side, us in time_in_turn(torch, stream, {"lc_gemm": lib, "hipblaslt": blas}, reps).items():
+            row[side] = {"us": round(us, 1), "tflops": round(2 * M * N * K / (us * 1e-6) / 1e12, 1)}
         row["ratio"] = round(row["hipblaslt"]["us"] / row["lc_gemm"]["us"], 3)
         print(f"[bench] {name} {lay} {M}x{N}x{K}: lc {row['lc_gemm']['us']} us, hipBLASLt "
               f"{row['hipblaslt']['us']} us", file=sys.stderr, flush=True)
         out.append(row)
         del a, b, c
-    return {"workload": cfg.name, "timing": f"{reps} launches back to back between HIP events",
+    return {"workload": cfg.name, "timing": f"rounds of {reps} launches, both sides in turn, medians",
             "shapes": out}
 
 
