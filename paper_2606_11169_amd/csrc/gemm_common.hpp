@@ -103,16 +103,52 @@ struct Tile {
 };
 template <int BM>
 __device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile &t) {
-  // Workgroup wg runs on XCD wg % 8, which gets nwg / 8 tiles; the 128 tile, which reads
-  // its operands twice as often as the 256 tile, in grids of over a round also where nwg is no
-  // multiple of 8 (the first nwg % 8 XCDs take one more: 1044 tiles at K = 4096 161 us, 197 in
-  // launch order, 356 tiles at K = 2048 42 and 58; 259 tiles +-5%, the 256 tile up to 5% slower,
-  // the 64 tile 4%). Not
-  // grouped rows, whose grid is an upper bound: the last XCDs would have nothing to do (60
-  // groups of 10 rows 13 -> 18 us).
-  if ((nwg & 7) == 0) wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
-  else if (BM == 128 && nwg > 264 && p.gmode != LC_GROUP_ROWS)
-    wg = (wg & 7) * (nwg >> 3) + min(wg & 7, nwg & 7) + (wg >> 3);
+  // Workgroup wg runs on XCD wg % 8; mapped, XCD x takes a run of n / 8 tiles (the first n %
+  // 8 one more). The 256, 64 and 32 tiles: grids of a multiple of 8 (others +-5%). The 128
+  // tile, which reads its operands twice as often as the 256 tile, also other grids of over a
+  // round with k enough for it to matter (1044 tiles at K = 4096 161 us, 197 in launch order,
+  // 356 tiles at K = 2048 42 and 58; 975 at K = 128 22.7 and 21.1), and grouped rows over
+  // the tiles that there are, found with a lane per group (at most 64): the grid is an upper
+  // bound, and a map over it leaves the last XCD the empty ones (60 groups of 10 rows 18 us, 13
+  // in launch order; 16 experts of about 690 rows x 1280 at K = 576 46 us in launch order, now
+  // 35; 8 of about 1290 x 1920 at K = 1856 130, now 93). The map is selects, not a branch, with which
+  // the compiler waits for all of a stage's fragments at once in some epilogues' main loops
+  // (residual at K = 4096, 76 tiles: 30.9 us, selects 29.7).
+  if constexpr (BM == 128) {
+    bool map = (nwg & 7) == 0 || (nwg > 264 && p.K >= 512);
+    int n = nwg, first = 0, last = 0, end = 0, nt = 0;
+    if (p.gmode == LC_GROUP_ROWS) {
+      const int lane = threadIdx.x & 63;
+      if (lane < p.ngroups) {
+        first = min(max(p.goff[lane], 0), p.M);
+        last = min(max(p.goff[lane + 1], first), p.M);
+      }
+      nt = end = (last - first + BM - 1) / BM;
+#pragma unroll
+      for (int d = 1; d < 64; d *= 2) {
+        const int e = __shfl_up(end, d);
+        end += lane >= d ? e : 0;
+      }
+      n = __builtin_amdgcn_readlane(end, 63) * p.tiles_n;
+      if (wg >= n) return false;
+      map = n > 264 && p.K >= 512;
+    }
+    const int x = map ? wg & 7 : 0;
+    wg = x * (n >> 3) + min(x, n & 7) + (map ? wg >> 3 : wg);
+    if (p.gmode == LC_GROUP_ROWS) {  // row tiles in the groups' order, all columns of one first
+      const int slot = wg / p.tiles_n, g = __builtin_ctzll(__ballot(end > slot));
+      t.tn = wg % p.tiles_n;
+      t.m0 = __builtin_amdgcn_readlane(first, g) + (slot - __builtin_amdgcn_readlane(end - nt, g)) * BM;
+      t.m_lim = __builtin_amdgcn_readlane(last, g);
+      t.kbeg = 0;
+      t.kend = p.K;
+      t.B = p.B + (int64_t)g * p.gstride_b;
+      t.C = p.C;
+      return true;
+    }
+  } else if ((nwg & 7) == 0) {
+    wg = (wg & 7) * (nwg >> 3) + (wg >> 3);
+  }
   t.m_lim = p.M;
   t.kbeg = 0;
   t.kend = p.K;

@@ -208,6 +208,31 @@ def test_tiles_grouped(sizes, N):
         assert torch.equal(D[e].double(), 1 + X[r].double().t() @ Y[r].double()), e
 
 
+@pytest.mark.parametrize("sizes,N,K", [
+    ([900, 0, 2000, 129, 1, 1671, 128, 700], 1160, 520), ([33 * i % 257 for i in range(64)], 520, 512),
+    ([0, 0, 0, 12000], 264, 520), ([700, 0, 1300, 128, 1, 900], 1416, 504)],
+    ids=["uneven", "64groups", "one", "few_k"])
+def test_tiles_grouped_mapped_to_xcds(sizes, N, K):
+    """Over 264 tiles of 128, which the map spreads over the XCDs by the tiles that the groups
+    have (few_k: in launch order): every row of a group, none past the last. Integers: exact."""
+    banner(f"gemm tiles grouped, mapped {len(sizes)} groups N={N} K={K}")
+    assert sum(-(-n // 128) for n in sizes) * -(-N // 128) > 264
+    g = gen(N + K)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    G, R = len(sizes), int(off[-1]) + 40
+    offd = torch.from_numpy(off).to(DEV)
+    A, B = ints(g, R, K), ints(g, G, N, K)
+    Bt = B.transpose(1, 2).contiguous()
+    for b, kmajor in ((B, 1), (Bt, 0)):
+        C = torch.full((R, N), -3.0, dtype=torch.float32, device=DEV)
+        lc.lc_gemm(BF16, lc.LC_EPI_STORE_F32, R, N, K, A, K, 1, b, K if kmajor else N, kmajor, C, N,
+                   group_mode=1, n_groups=G, group_offsets=offd, group_stride_b=N * K)
+        for e in range(G):
+            r = slice(off[e], off[e + 1])
+            assert torch.equal(C[r].double(), A[r].double() @ B[e].double().t()), e
+        assert bool((C[off[-1]:] == -3.0).all())
+
+
 def test_widest_grouped_output():
     """64 groups, eight of one row each, of 30 million columns: the smaller tiles' upper
     bound of workgroups passes what a launch takes. Integer operands: exact."""
