@@ -536,19 +536,20 @@ static lc_status check_gemm_args(const lc_gemm_args &a) {
 
 // Output tile of a product: the one whose grid is expected to take the least time. One
 // workgroup runs per compute unit with every tile size, so a grid of t tiles takes
-// ceil(t / 256) rounds. Measured (2048 x 2048 to 4096 x 11008 outputs, all compute units
-// busy) ns per k and round: 26 with 256 x 256 tiles, 8.2 with 128 x 128, 4.4 with 64 x 64,
-// about 2.2 with 32 x 32 (1.3 on a half-full chip); a 256 x 256 round that fills only part of
-// the chip takes 17.7 + 8.3 x the part. And us per round besides (first loads, epilogue): 8,
-// 3.9, 3.0 and 1.5, of weight gradients (neither operand k-major; fp32 output) 19, 6.8, 5.2
-// and 2.6. The larger tile does more work per round, the smaller ones fill the
-// chip: 2048 x 2048 outputs (64, 256 or 1024 tiles) at K = 5632 take 107, 49 or 103 us; 2048 x
+// ceil(t / 256) rounds. Fitted to 2000 products of 64 x 336 to 8448 x 7728 outputs at K =
+// 128 to 4096, ns per k and round: 21 with 256 x 256 tiles, 7.2 with 128 x 128, 3.8 with 64
+// x 64, 1.9 with 32 x 32; a 256 x 256 round that fills only part of the chip takes 16.5 + 4.5
+// x the part. And us per round besides (first loads, epilogue): 8, 3.8, 2.8 and 1.4, where
+// the epilogue moves 8 to 12 bytes per output (fp32 gradients and residual rows, SwiGLU
+// backward) 20, 8, 6 and 3. The larger tile does more work per round, the smaller ones fill
+// the chip: 2048 x 2048 outputs (64, 256 or 1024 tiles) at K = 5632 take 107, 49 or 103 us; 2048 x
 // 6144 at K = 2048 (192, 768 or 3072 tiles) 53, 60 or 135 us; 256 x 512 at K = 1408 (2, 8, 32 or
 // 128 tiles) 31, 13, 9 or 6 us; 256 x 1536 at K = 512 with 64 or 32 (96 or 384 tiles) 6.5 or 6.8.
-// Just over a round of 256 tiles, with few k the second round of 256 is the cheaper one: 2304
-// x 7424 (261 or 1044 tiles) NT at K = 128, 512, 2048 23, 37, 94 or 25, 38, 88 us. The choice
-// depends on sizes, layout and grouping only, so products of the same shape add in the same
-// order whatever their epilogue (an accumulated and a stored gradient are the same bits).
+// A few tiles over whole rounds of 256: 2304 x 7424 (261 or 1044 tiles) NT at K = 128, 512, 2048
+// 23, 37, 94 or 25, 38, 88 us; 3072 x 10880 (516 or 2040) at K = 2048 NT 150 or 161, SwiGLU
+// backward 213 or 253; 3072 x 5632 (264 or 1056) with a residual at K = 1024 66 or 58. The
+// choice depends on sizes, layout, grouping and those two epilogues only, so an accumulated
+// and a stored gradient add in one order (the same bits).
 static int pick_tile(const lc_gemm_args &a) {
   const int64_t N = a.epilogue == LC_EPI_SWIGLU ? 2 * a.N : a.N;
   auto tiles = [&](int64_t t) {
@@ -561,13 +562,14 @@ static int pick_tile(const lc_gemm_args &a) {
   constexpr int64_t CU = 256;
   // 0.1 ns: k (a group's share of it) times the round's rate, and what a round costs besides
   const int64_t K = a.group_mode == LC_GROUP_K ? a.K / a.n_groups : a.K;
-  const bool wgrad = !a.a_kmajor && !a.b_kmajor;
-  const int64_t f256 = wgrad ? 190000 : 80000, f128 = wgrad ? 68000 : 39000, f64 = wgrad ? 52000 : 30000;
+  const bool heavy = (!a.a_kmajor && !a.b_kmajor) || a.epilogue == LC_EPI_RESIDUAL ||
+                     a.epilogue == LC_EPI_SWIGLU_BWD;
+  const int64_t f256 = heavy ? 200000 : 80000, f128 = heavy ? 80000 : 38000, f64 = heavy ? 60000 : 28000;
   const int64_t t256 = tiles(256), part = t256 % CU;
-  const int64_t c256 = t256 / CU * (260 * K + f256) + (part ? (177 + 83 * part / CU) * K + f256 : 0);
-  const int64_t c128 = (tiles(128) + CU - 1) / CU * (82 * K + f128);
-  const int64_t c64 = (tiles(64) + CU - 1) / CU * (44 * K + f64);
-  const int64_t c32 = (tiles(32) + CU - 1) / CU * (22 * K + f64 / 2);
+  const int64_t c256 = t256 / CU * (210 * K + f256) + (part ? (165 + 45 * part / CU) * K + f256 : 0);
+  const int64_t c128 = (tiles(128) + CU - 1) / CU * (72 * K + f128);
+  const int64_t c64 = (tiles(64) + CU - 1) / CU * (38 * K + f64);
+  const int64_t c32 = (tiles(32) + CU - 1) / CU * (19 * K + f64 / 2);
   int t = c128 < c256 ? 128 : 256;
   if (c64 < c128 && c64 < c256) t = 64;
   if (c32 < c64 && c32 < c128 && c32 < c256) t = 32;
