@@ -101,7 +101,8 @@ struct Tile {
   const bf16_t *B;
   void *C;
 };
-template <int BM>
+// ROWS: grouped rows or not where the kernel is for one of them (128 tile), -1 by p.gmode
+template <int BM, int ROWS = -1>
 __device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile &t) {
   // Workgroup wg runs on XCD wg % 8; mapped, XCD x takes a run of n / 8 tiles (the first n %
   // 8 one more). The 256, 64 and 32 tiles: grids of a multiple of 8 (others +-5%). The 128
@@ -115,9 +116,10 @@ __device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile 
   // the compiler waits for all of a stage's fragments at once in some epilogues' main loops
   // (residual at K = 4096, 76 tiles: 30.9 us, selects 29.7).
   if constexpr (BM == 128) {
+    const bool rows = ROWS < 0 ? p.gmode == LC_GROUP_ROWS : ROWS > 0;
     bool map = (nwg & 7) == 0 || (nwg > 264 && p.K >= 512);
     int n = nwg, first = 0, last = 0, end = 0, nt = 0;
-    if (p.gmode == LC_GROUP_ROWS) {
+    if (rows) {
       const int lane = threadIdx.x & 63;
       if (lane < p.ngroups) {
         first = min(max(p.goff[lane], 0), p.M);
@@ -135,7 +137,7 @@ __device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile 
     }
     const int x = map ? wg & 7 : 0;
     wg = x * (n >> 3) + min(x, n & 7) + (map ? wg >> 3 : wg);
-    if (p.gmode == LC_GROUP_ROWS) {  // row tiles in the groups' order, all columns of one first
+    if (rows) {  // row tiles in the groups' order, all columns of one first
       const int slot = wg / p.tiles_n, g = __builtin_ctzll(__ballot(end > slot));
       t.tn = wg % p.tiles_n;
       t.m0 = __builtin_amdgcn_readlane(first, g) + (slot - __builtin_amdgcn_readlane(end - nt, g)) * BM;
@@ -154,7 +156,7 @@ __device__ __forceinline__ bool find_tile(const GemmP &p, int wg, int nwg, Tile 
   t.kend = p.K;
   t.B = p.B;
   t.C = p.C;
-  if (p.gmode == LC_GROUP_ROWS) {
+  if (BM != 128 && p.gmode == LC_GROUP_ROWS) {
     // tile slot wg / tiles_n walks the groups' row tiles in order; slots past
     // the last group's tiles have nothing to do (the grid is an upper bound)
     t.tn = wg % p.tiles_n;

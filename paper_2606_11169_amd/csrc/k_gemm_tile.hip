@@ -118,7 +118,7 @@ struct Opnd {
 template <int T> constexpr int ring_bytes() { return NST * 2 * Cfg<T>::SUB * (T / 8) * RUN; }
 
 // One workgroup's part: tile wg of nwg (ring: ring_bytes<T>() of LDS)
-template <int T, bool A_K, bool B_K, int EPI, int TM>
+template <int T, bool A_K, bool B_K, int EPI, int TM, int ROWS = -1>
 __device__ __forceinline__ void tile_block(GemmP p, int wg, int nwg, lds_t *R0) {
   using C = Cfg<T>;
   constexpr int NT = threads(T), NW = NT / 64, KS = 64 * C::SUB;
@@ -136,7 +136,7 @@ __device__ __forceinline__ void tile_block(GemmP p, int wg, int nwg, lds_t *R0) 
   constexpr bool SWI = EPI == LC_EPI_SWIGLU;
   constexpr int MAPB = SWI ? B_SWIGLU : EPI == LC_EPI_ROPE ? B_ROPE : B_PLAIN;
   Tile tile;
-  if (!find_tile<T>(p, wg, nwg, tile)) return;  // before any barrier
+  if (!find_tile<T, ROWS>(p, wg, nwg, tile)) return;  // before any barrier
   const int m0 = tile.m0, m_lim = tile.m_lim, kbeg = tile.kbeg, kend = tile.kend;
   const int n0 = SWI ? tile.tn * (T / 2) : tile.tn * T;
 
@@ -339,10 +339,24 @@ __device__ __forceinline__ void tile_block(GemmP p, int wg, int nwg, lds_t *R0) 
   }
 }
 
+// (residual products are never grouped)
+constexpr bool splits_rows(int epi) { return epi == LC_EPI_STORE || epi == LC_EPI_ACCUM_F32; }
+
 template <int T, bool A_K, bool B_K, int EPI, int TM>
 __global__ __launch_bounds__(threads(T)) void gemm_tile_kernel(GemmP p) {
   __shared__ __align__(16) char ring[ring_bytes<T>()];
-  tile_block<T, A_K, B_K, EPI, TM>(p, (int)blockIdx.x, (int)gridDim.x, LDS_AS(char, ring));
+  constexpr bool SPLIT = T == 128 && (splits_rows(EPI) || EPI == LC_EPI_RESIDUAL);
+  tile_block<T, A_K, B_K, EPI, TM, SPLIT ? 0 : -1>(p, (int)blockIdx.x, (int)gridDim.x, LDS_AS(char, ring));
+}
+
+// Grouped rows in 128 tiles, of plain and accumulating products: in a kernel of their own, as
+// the search for a tile's group costs the others 0.2 to 0.5 us a launch (8 of the 145
+// launches of a small bf16 step, d 512: 958 us, now 955). The fused epilogues keep both in one
+// kernel, whose main loop the compiler schedules better (RoPE and SwiGLU 3%).
+template <bool A_K, bool B_K, int EPI, int TM>
+__global__ __launch_bounds__(threads(128)) void gemm_tile_rows_kernel(GemmP p) {
+  __shared__ __align__(16) char ring[ring_bytes<128>()];
+  tile_block<128, A_K, B_K, EPI, TM, 1>(p, (int)blockIdx.x, (int)gridDim.x, LDS_AS(char, ring));
 }
 
 // An input gradient's nx tiles and a weight gradient's nw in one grid: two products
@@ -365,6 +379,12 @@ lc_status launch_t(const GemmP &p, int tile, hipStream_t s) {
   unsigned grid = (unsigned)p.tiles_m * (unsigned)p.tiles_n;
   if (p.gmode == LC_GROUP_ROWS) grid = (unsigned)(p.tiles_m + p.ngroups) * (unsigned)p.tiles_n;
   if (p.gmode == LC_GROUP_K) grid *= (unsigned)p.ngroups;
+  if constexpr (splits_rows(EPI)) {
+    if (tile == 128 && p.gmode == LC_GROUP_ROWS) {
+      hipLaunchKernelGGL((gemm_tile_rows_kernel<A_K, B_K, EPI, TM>), dim3(grid), dim3(threads(128)), 0, s, p);
+      return check_launch("gemm_tile_rows_kernel");
+    }
+  }
   if (tile == 128)
     hipLaunchKernelGGL((gemm_tile_kernel<128, A_K, B_K, EPI, TM>), dim3(grid), dim3(threads(128)), 0, s, p);
   else if (tile == 64)
